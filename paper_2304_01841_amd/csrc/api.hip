@@ -196,6 +196,8 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc)
             if ((int64_t)pl->N2 / R * 2 > 1024LL * (32 / R))
                 return fail(WCSIM_E_INVALID, "tick transform too large for one workgroup");
         }
+        if (!make_tick_plan(pl))
+            return fail(WCSIM_E_INVALID, "tick transform too large for one workgroup");
     }
     pl->L = L;
     pl->V = L - pl->Rp + 1;
@@ -1047,9 +1049,9 @@ ChunkLayout plan_chunk(const wcsim_plane *const *planes, const int64_t *n,
         L.n_total += n[idx[(size_t)k]];
         L.ntiles_total += pl->ntiles;
         L.nbands_total += occ_bands(pl->Np);
-        L.nblk_r += rows_blocks((int)pl->Np);
+        L.nblk_r += rows_blocks(pl, (int)pl->Np);
         L.nblk_p += L.poly ? poly_blocks_total(pl) : pitch_blocks_total(pl);
-        L.nblk_c += rows_blocks((int)nout);
+        L.nblk_c += rows_blocks(pl, (int)nout);
     }
     bd[nev] = (int32_t)L.n_total;
     bt[nev] = (int32_t)L.ntiles_total;

@@ -176,6 +176,89 @@ __device__ __forceinline__ void dft<16>(float2 *x)
     }
 }
 
+// N1 x N2 points with N1, N2 coprime, without factors between the two stages
+// (the Good-Thomas index maps n = N2 n1 + N1 n2, m = K1 m1 + K2 m2 modulo N1 N2,
+// K1 = 1 mod N1 and 0 mod N2, K2 the reverse).
+template <int N1, int N2, int K1, int K2>
+__device__ __forceinline__ void dft_coprime(float2 *x)
+{
+    constexpr int N = N1 * N2;
+    static_assert(K1 % N1 == 1 && K1 % N2 == 0 && K2 % N1 == 0 && K2 % N2 == 1, "index maps");
+    float2 a[N1][N2];
+#pragma unroll
+    for (int n1 = 0; n1 < N1; ++n1) {
+#pragma unroll
+        for (int n2 = 0; n2 < N2; ++n2)
+            a[n1][n2] = x[(N2 * n1 + N1 * n2) % N];
+        dft<N2>(a[n1]);
+    }
+#pragma unroll
+    for (int m2 = 0; m2 < N2; ++m2) {
+        float2 b[N1];
+#pragma unroll
+        for (int n1 = 0; n1 < N1; ++n1)
+            b[n1] = a[n1][m2];
+        dft<N1>(b);
+#pragma unroll
+        for (int m1 = 0; m1 < N1; ++m1)
+            x[(K1 * m1 + K2 * m2) % N] = b[m1];
+    }
+}
+
+template <>
+__device__ __forceinline__ void dft<6>(float2 *x)
+{
+    dft_coprime<2, 3, 3, 4>(x);
+}
+template <>
+__device__ __forceinline__ void dft<10>(float2 *x)
+{
+    dft_coprime<2, 5, 5, 6>(x);
+}
+template <>
+__device__ __forceinline__ void dft<12>(float2 *x)
+{
+    dft_coprime<4, 3, 9, 4>(x);
+}
+template <>
+__device__ __forceinline__ void dft<15>(float2 *x)
+{
+    dft_coprime<3, 5, 10, 6>(x);
+}
+
+// 9 points as 3 x 3: t = 3 t1 + t2, m = m1 + 3 m2; 3-point DFTs over t1, the
+// factors exp(-2 pi i t2 m1 / 9), then 3-point DFTs over t2.
+template <>
+__device__ __forceinline__ void dft<9>(float2 *x)
+{
+    constexpr float c1 = 0.76604444311897803520f;  // cos(2 pi / 9)
+    constexpr float s1 = 0.64278760968653932632f;  // sin(2 pi / 9)
+    constexpr float c2 = 0.17364817766693034885f;  // cos(4 pi / 9)
+    constexpr float s2 = 0.98480775301220805937f;  // sin(4 pi / 9)
+    constexpr float c4 = -0.93969262078590838405f;  // cos(8 pi / 9)
+    constexpr float s4 = 0.34202014332566873304f;   // sin(8 pi / 9)
+    float2 a[3][3];
+#pragma unroll
+    for (int t2 = 0; t2 < 3; ++t2) {
+        a[t2][0] = x[t2];
+        a[t2][1] = x[3 + t2];
+        a[t2][2] = x[6 + t2];
+        dft<3>(a[t2]);
+    }
+    a[1][1] = cmul(a[1][1], make_float2(c1, -s1));
+    a[1][2] = cmul(a[1][2], make_float2(c2, -s2));
+    a[2][1] = cmul(a[2][1], make_float2(c2, -s2));
+    a[2][2] = cmul(a[2][2], make_float2(c4, -s4));
+#pragma unroll
+    for (int m1 = 0; m1 < 3; ++m1) {
+        float2 b[3] = {a[0][m1], a[1][m1], a[2][m1]};
+        dft<3>(b);
+#pragma unroll
+        for (int m2 = 0; m2 < 3; ++m2)
+            x[m1 + 3 * m2] = b[m2];
+    }
+}
+
 // Multiply x_t by w^t, t = 1..R-1 (powers by repeated products: a few ulp,
 // far below the float32 transform error).
 template <int R>
@@ -417,6 +500,7 @@ template <int N, int NSS, int SS, int ES, int NT, int... Rs>
 struct FftCt {
     static constexpr int kThreads = NT;
     static constexpr int kMaxThreads = NT;
+    static constexpr int kMinWaves = 1;  // (no constraint)
     __device__ __forceinline__ void run(float2 *buf, const float2 *tab) const
     {
         InLds in, out;
@@ -427,6 +511,157 @@ struct FftCt {
                                            Store store) const
     {
         ct_fft<N, NSS, SS, ES, NT, 1, Load, Store, Rs...>(buf, tab, load, store);
+    }
+};
+
+// ---------------------------------------------------------------------------
+// Tick-axis transform of any supported length.  Row threadIdx.y of the
+// workgroup is one sequence; a pass of radix R gives each of its threads up to
+// gen_per_thread(R) butterflies, so that 16 values are in registers for every
+// radix.  The plan (chosen on the host, gen_plan) takes few passes of large
+// radices: a pass costs an LDS round trip of the row and two barriers whatever
+// its radix, and these passes are bound by that latency and by LDS traffic, not
+// by the butterflies' arithmetic.  The sizes are run-time values: k = i mod p
+// is a multiply by a reciprocal held per pass (an integer division would be
+// the longest part of a small butterfly).
+// A pass's factors w^t are products of at most three each of w and w^4, both
+// read from the table, so that the factors of a radix-16 pass are no further off
+// than those of a radix-8 pass by repeated products of w.
+// Measured against radix-2..8 passes with a copy through LDS at both ends: 4800
+// rows of 1600 points forward 122 -> 42 us, inverse 86 -> 42 us (2.8 TB/s of the
+// rows and spectra); 3330 rows of 2187 points forward 79 -> 28 us.
+// ---------------------------------------------------------------------------
+constexpr int gen_per_thread(int R) { return R >= 9 ? 1 : 16 / R; }
+
+// x_t *= w^t, w = exp(-2 pi i j / n) for table index j.
+template <int R>
+__device__ __forceinline__ void gen_twiddle(float2 *x, const float2 *tab, int j)
+{
+    float2 w[4];
+    w[1] = tw_at(tab, j);
+    if constexpr (R > 2)
+        w[2] = cmul(w[1], w[1]);
+    if constexpr (R > 3)
+        w[3] = cmul(w[2], w[1]);
+    float2 h = make_float2(1.0f, 0.0f);  // w^(4 (t / 4))
+    float2 w4 = h;
+    if constexpr (R > 4)
+        w4 = tw_at(tab, 4 * j);
+#pragma unroll
+    for (int t = 1; t < R; ++t) {
+        if (t % 4 == 0)
+            h = (t == 4) ? w4 : cmul(h, w4);
+        const float2 f = (t < 4) ? w[t] : (t % 4 == 0) ? h : cmul(h, w[t % 4]);
+        x[t] = cmul(x[t], f);
+    }
+}
+
+// One Stockham pass of radix R on this thread's row (see stockham_pass for the
+// indices).  GLOAD: inputs from load(s, n), every load issued from a valid
+// index (a surplus butterfly takes the last one's inputs); GSTORE: outputs to
+// store(s, n, value).
+template <int R, bool GLOAD, bool GSTORE, class Load, class Store>
+__device__ __forceinline__ void gen_pass(float2 *row, const float2 *tab, const GenPlan &plan, int q,
+                                         Load &load, Store &store)
+{
+    constexpr int MAXB = gen_per_thread(R);
+    const int nb = plan.nb[q], p = plan.p[q];
+    const int tx = threadIdx.x, TX = blockDim.x, s = threadIdx.y;
+    float2 v[MAXB][R];
+#pragma unroll
+    for (int b = 0; b < MAXB; ++b) {
+        const int i = tx + b * TX;
+        if constexpr (GLOAD) {
+            const int ic = min(i, nb - 1);
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+                v[b][t] = load(s, ic + t * nb);
+        } else if (i < nb) {
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+                v[b][t] = row[i + t * nb];
+        }
+    }
+    if constexpr (!GLOAD)
+        __syncthreads();  // every input is read before any output lands in LDS
+#pragma unroll
+    for (int b = 0; b < MAXB; ++b) {
+        const int i = tx + b * TX;
+        if (i < nb) {
+            int k = 0;
+            if (p > 1) {
+                k = i - (int)__umulhi((uint32_t)i, plan.magic[q]) * p;
+                gen_twiddle<R>(v[b], tab, k * plan.tws[q]);
+            }
+            dft<R>(v[b]);
+            const int n0 = (i - k) * R + k;
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                if constexpr (GSTORE)
+                    store(s, n0 + t * p, v[b][t]);
+                else
+                    row[n0 + t * p] = v[b][t];
+            }
+        }
+    }
+    if constexpr (!GSTORE)
+        __syncthreads();
+}
+
+template <bool GLOAD, bool GSTORE, class Load, class Store>
+__device__ __forceinline__ void gen_pass_any(float2 *row, const float2 *tab, const GenPlan &plan,
+                                             int q, Load &load, Store &store)
+{
+    switch (plan.radix[q]) {
+    case 16:
+        return gen_pass<16, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 15:
+        return gen_pass<15, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 12:
+        return gen_pass<12, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 10:
+        return gen_pass<10, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 9:
+        return gen_pass<9, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 8:
+        return gen_pass<8, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 6:
+        return gen_pass<6, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 5:
+        return gen_pass<5, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 4:
+        return gen_pass<4, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    case 3:
+        return gen_pass<3, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    default:
+        return gen_pass<2, GLOAD, GSTORE>(row, tab, plan, q, load, store);
+    }
+}
+
+struct FftGen {
+    static constexpr int kMaxThreads = 1024;
+    // Wavefronts per SIMD that the register allocation aims at: the radix-16
+    // pass would take 98 registers (4 wavefronts); held to 80, passes A and C of
+    // 4800 rows of 1600 points take 5% less time, and at 8 wavefronts (64
+    // registers) longer rows lose more than that again.
+    static constexpr int kMinWaves = 6;
+    GenPlan plan;
+    template <class Load, class Store>
+    __device__ __forceinline__ void run_io(float2 *buf, const float2 *tab, Load load,
+                                           Store store) const
+    {
+        constexpr bool kLoad = !std::is_same<Load, InLds>::value;
+        constexpr bool kStore = !std::is_same<Store, InLds>::value;
+        static_assert(kLoad != kStore, "one end of a tick-axis transform is global memory");
+        float2 *row = buf + (size_t)threadIdx.y * (plan.n + 1);
+        const int last = plan.npass - 1;
+        InLds none;
+        if constexpr (kLoad)
+            gen_pass_any<true, false>(row, tab, plan, 0, load, none);
+        for (int q = kLoad ? 1 : 0; q < last + (kLoad ? 1 : 0); ++q)
+            gen_pass_any<false, false>(row, tab, plan, q, none, none);
+        if constexpr (kStore)
+            gen_pass_any<false, true>(row, tab, plan, last, none, store);
     }
 };
 
@@ -455,8 +690,7 @@ __device__ __forceinline__ void batched_copy(int total, LoadF load, StoreF store
     }
 }
 
-// Twiddle tables (global) of a kernel, copied into LDS.  Both tables have at
-// most blockDim.x entries (checked on the host).
+// Twiddle tables (global) of a kernel, copied into LDS.
 struct TwTables {
     const float2 *a;
     int na;
@@ -466,13 +700,15 @@ struct TwTables {
 
 __device__ __forceinline__ void load_tables(const TwTables &t, float2 *la, float2 *lb)
 {
-    const int tid = threadIdx.x;
-    const float2 va = (tid < t.na) ? t.a[tid] : make_float2(0.0f, 0.0f);
-    const float2 vb = (t.b && tid < t.nb) ? t.b[tid] : make_float2(0.0f, 0.0f);
-    if (tid < t.na)
-        la[tid] = va;
-    if (t.b && tid < t.nb)
-        lb[tid] = vb;
+    const int step = blockDim.x * blockDim.y;
+    for (int i = threadIdx.y * blockDim.x + threadIdx.x; i < max(t.na, t.nb); i += step) {
+        const float2 va = (i < t.na) ? t.a[i] : make_float2(0.0f, 0.0f);
+        const float2 vb = (t.b && i < t.nb) ? t.b[i] : make_float2(0.0f, 0.0f);
+        if (i < t.na)
+            la[i] = va;
+        if (t.b && i < t.nb)
+            lb[i] = vb;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -482,7 +718,8 @@ __device__ __forceinline__ void load_tables(const TwTables &t, float2 *la, float
 // E_k = (Z_k + conj Z_{N2-k}) / 2, D_k = (Z_k - conj Z_{N2-k}) / 2 and
 // w = exp(-2 pi i / N').  Output chunk layout X[c][row][f], k = c F + f,
 // frequencies above N2 zero.
-// LDS: rows [RPW][N2 + 1], then the N2 table, then the N' table.
+// Workgroups of (threads of a row, rows): thread (x, y) works on row y alone.
+// LDS: rows [rows][N2 + 1], then the N2 table, then the N' table.
 // ---------------------------------------------------------------------------
 // Rows of one tick-axis forward launch; in a batch, taken from the event that
 // owns the workgroup.
@@ -500,9 +737,10 @@ struct R2CIo {
 __device__ const float2 g_zero_pair[1] = {};
 
 template <class FFT, bool BATCH>
-__global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_r2c(R2CIo io, BatchTables bt, int N2,
+__global__ __launch_bounds__(FFT::kMaxThreads)
+__attribute__((amdgpu_waves_per_eu(FFT::kMinWaves))) void k_rows_r2c(R2CIo io, BatchTables bt, int N2,
                                                               FFT fft, TwTables tw, int F_shift,
-                                                              int C, int rpw_shift)
+                                                              int C)
 {
     extern __shared__ float2 lds[];
     int blk = blockIdx.x;
@@ -522,26 +760,28 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_r2c(R2CIo io, BatchTa
     const int nrows = io.nrows, ncols = io.ncols;
     const int64_t in_stride = io.in_stride;
     const gptr<float2> X = glb(io.X);
-    const int RPW = 1 << rpw_shift;
     const int S = N2 + 1;
-    float2 *tabN2 = lds + RPW * S;
+    float2 *tabN2 = lds + (int)blockDim.y * S;
     float2 *tabH = tabN2 + tw.na;
     load_tables(tw, tabN2, tabH);
-    const int row0 = blk * RPW;
+    const int row0 = blk * (int)blockDim.y, my_row = row0 + (int)threadIdx.y;
+    const int F = 1 << F_shift, CF = C << F_shift;
+    auto put = [&](int k, float2 v) {
+        X[(((int64_t)(k >> F_shift) * nrows + my_row) << F_shift) + (k & (F - 1))] = v;
+    };
     // Bit c of occ_m: ticks c 2^osh .. (c + 1) 2^osh - 1 of this workgroup's
     // band of rows are occupied (every bit set without a map; a shift of 31
     // sends every tick to bit 0).
     uint64_t occ_m = ~0ull;
     int osh = 31;
     if (io.occ) {
-        occ_m = __ballot(io.occ[(row0 / kOccRows) * kOccCols + (threadIdx.x & 63)] != 0);
+        const int lane = (threadIdx.y * blockDim.x + threadIdx.x) & 63;
+        occ_m = __ballot(io.occ[(row0 / kOccRows) * kOccCols + lane] != 0);
         osh = io.occ_shift;
         if (occ_m == 0) {  // no depo reaches this band of rows: zero spectra
-            const int fmask = (1 << F_shift) - 1, cf = C << F_shift;
-            for (int s = 0; s < RPW && row0 + s < nrows; ++s)
-                for (int k = threadIdx.x; k < cf; k += blockDim.x)
-                    X[(((int64_t)(k >> F_shift) * nrows + row0 + s) << F_shift) + (k & fmask)] =
-                        make_float2(0.0f, 0.0f);
+            if (my_row < nrows)
+                for (int k = threadIdx.x; k < CF; k += blockDim.x)
+                    put(k, make_float2(0.0f, 0.0f));
             return;
         }
     }
@@ -576,29 +816,21 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_r2c(R2CIo io, BatchTa
         fft.run_io(lds, tabN2, load1, InLds{});
     // Unpacking straight to the output: the pair (k, N2 - k) goes from LDS to
     // its two chunk slots, and the padding frequencies above N2 get zeros.
+    if (my_row >= nrows)
+        return;
     const int half = N2 / 2;
-    const int F = 1 << F_shift;
-    const int CF = C << F_shift;
-    for (int s = 0; s < RPW; ++s) {
-        const int row = row0 + s;
-        if (row >= nrows)
-            break;
-        const float2 *b = lds + s * S;
-        auto put = [&](int k, float2 v) {
-            X[(((int64_t)(k >> F_shift) * nrows + row) << F_shift) + (k & (F - 1))] = v;
-        };
-        for (int k = threadIdx.x; k <= half; k += blockDim.x) {
-            const int kn = (k == 0) ? 0 : N2 - k;
-            const float2 Zk = b[k], Zn = b[kn];
-            const float2 E = make_float2(0.5f * (Zk.x + Zn.x), 0.5f * (Zk.y - Zn.y));
-            const float2 D = make_float2(0.5f * (Zk.x - Zn.x), 0.5f * (Zk.y + Zn.y));
-            const float2 wD = cmul(tw_at(tabH, k), D);
-            put(k, csub(E, mul_pi(wD)));
-            put((k == 0) ? N2 : kn, conjf2(cadd(E, mul_pi(wD))));
-        }
-        for (int k = N2 + 1 + threadIdx.x; k < CF; k += blockDim.x)
-            put(k, make_float2(0.0f, 0.0f));
+    const float2 *b = lds + (int)threadIdx.y * S;
+    for (int k = threadIdx.x; k <= half; k += blockDim.x) {
+        const int kn = (k == 0) ? 0 : N2 - k;
+        const float2 Zk = b[k], Zn = b[kn];
+        const float2 E = make_float2(0.5f * (Zk.x + Zn.x), 0.5f * (Zk.y - Zn.y));
+        const float2 D = make_float2(0.5f * (Zk.x - Zn.x), 0.5f * (Zk.y + Zn.y));
+        const float2 wD = cmul(tw_at(tabH, k), D);
+        put(k, csub(E, mul_pi(wD)));
+        put((k == 0) ? N2 : kn, conjf2(cadd(E, mul_pi(wD))));
     }
+    for (int k = N2 + 1 + threadIdx.x; k < CF; k += blockDim.x)
+        put(k, make_float2(0.0f, 0.0f));
 }
 
 // ---------------------------------------------------------------------------
@@ -606,8 +838,10 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_r2c(R2CIo io, BatchTa
 // Z_k = A_k + i conj(w^k) B_k with A_k = X_k + conj X_{N2-k},
 // B_k = X_k - conj X_{N2-k}; the unnormalised inverse FFT_N2 of Z gives
 // z_n = x_{2n} + i x_{2n+1}.  The inverse runs as a forward transform of
-// conj(Z) (conj of the result).
+// conj(Z) (conj of the result).  Each thread packs its pairs (k, N2 - k) from
+// global memory into LDS, kPackPairs pairs of loads in flight together.
 // ---------------------------------------------------------------------------
+constexpr int kPackPairs = 4;
 struct C2RIo {
     const float2 *Y;
     int nrows;
@@ -617,9 +851,10 @@ struct C2RIo {
 };
 
 template <class FFT, bool BATCH>
-__global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_c2r(C2RIo io, BatchTables bt, int N2,
+__global__ __launch_bounds__(FFT::kMaxThreads)
+__attribute__((amdgpu_waves_per_eu(FFT::kMinWaves))) void k_rows_c2r(C2RIo io, BatchTables bt, int N2,
                                                               FFT fft, TwTables tw, int F_shift,
-                                                              int C, int rpw_shift)
+                                                              int C)
 {
     extern __shared__ float2 lds[];
     int blk = blockIdx.x;
@@ -637,46 +872,42 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_rows_c2r(C2RIo io, BatchTa
     const int nrows = io.nrows, ncols = io.ncols;
     const gptr<float> out = glb(io.out);
     const int64_t out_stride = io.out_stride;
-    const int RPW = 1 << rpw_shift;
     const int S = N2 + 1;
-    float2 *tabN2 = lds + RPW * S;
+    float2 *tabN2 = lds + (int)blockDim.y * S;
     float2 *tabH = tabN2 + tw.na;
     load_tables(tw, tabN2, tabH);
-    const int row0 = blk * RPW;
+    const int row0 = blk * (int)blockDim.y;
     const int F = 1 << F_shift;
-    const int total = C << (F_shift + rpw_shift);
-    batched_copy(
-        total,
-        [&](int g) {
-            const int f = g & (F - 1);
-            const int s = (g >> F_shift) & (RPW - 1);
-            const int c = g >> (F_shift + rpw_shift);
-            const int row = row0 + s;
-            if (row >= nrows)
-                return make_float2(0.0f, 0.0f);
-            const float2 v = Y[(((int64_t)c * nrows + row) << F_shift) + f];
-            return v;
-        },
-        [&](int g, float2 v) {
-            const int f = g & (F - 1);
-            const int s = (g >> F_shift) & (RPW - 1);
-            const int k = ((g >> (F_shift + rpw_shift)) << F_shift) + f;
-            if (k <= N2)
-                lds[s * S + k] = v;
-        });
-    __syncthreads();
+    const int my_row = min(row0 + (int)threadIdx.y, nrows - 1);  // (a surplus row repeats the last)
+    auto get = [&](int k) {
+        return Y[(((int64_t)(k >> F_shift) * nrows + my_row) << F_shift) + (k & (F - 1))];
+    };
     const int half = N2 / 2;
-    for (int s = 0; s < RPW; ++s) {
-        float2 *b = lds + s * S;
-        for (int k = threadIdx.x; k <= half; k += blockDim.x) {
-            const int kn = (k == 0) ? N2 : N2 - k;
-            const float2 Xk = b[k], Xn = b[kn];
-            const float2 A = make_float2(Xk.x + Xn.x, Xk.y - Xn.y);
-            const float2 B = make_float2(Xk.x - Xn.x, Xk.y + Xn.y);
-            const float2 wB = cmul(conjf2(tw_at(tabH, k)), B);
-            b[k] = conjf2(cadd(A, mul_pi(wB)));
-            if (k != 0)
-                b[kn] = csub(A, mul_pi(wB));  // conj of conj(A - i conj(w) B)
+    float2 *b = lds + (int)threadIdx.y * S;
+    bool tables = false;  // the tables are visible to every thread
+    for (int k0 = threadIdx.x; k0 <= half || !tables; k0 += kPackPairs * blockDim.x) {
+        float2 xk[kPackPairs], xn[kPackPairs];
+#pragma unroll
+        for (int u = 0; u < kPackPairs; ++u) {
+            const int k = min(k0 + u * (int)blockDim.x, half);
+            xk[u] = get(k);
+            xn[u] = get(N2 - k);
+        }
+        if (!tables) {
+            __syncthreads();
+            tables = true;
+        }
+#pragma unroll
+        for (int u = 0; u < kPackPairs; ++u) {
+            const int k = k0 + u * (int)blockDim.x;
+            if (k <= half) {
+                const float2 A = make_float2(xk[u].x + xn[u].x, xk[u].y - xn[u].y);
+                const float2 B = make_float2(xk[u].x - xn[u].x, xk[u].y + xn[u].y);
+                const float2 wB = cmul(conjf2(tw_at(tabH, k)), B);
+                b[k] = conjf2(cadd(A, mul_pi(wB)));
+                if (k != 0)
+                    b[N2 - k] = csub(A, mul_pi(wB));  // conj of conj(A - i conj(w) B)
+            }
         }
     }
     __syncthreads();
@@ -1025,13 +1256,6 @@ int threads_for(const FftPlan &plan, int nseq)
     return threads;
 }
 
-// Rows per workgroup in passes A and C.  One row keeps a workgroup's LDS at
-// one row (25 KB for N2 = 3125), so six workgroups share a CU and the global
-// loads of some overlap the transforms of others; two rows per workgroup
-// halve that overlap and measured slower.
-constexpr int kRowsShift = 0;
-constexpr int kRowsPerBlock = 1 << kRowsShift;
-
 // Compile-time transforms for the sizes the schedules use:
 //   tick axis N2 = 3125 (N' = 6250, 6000-tick planes; 320 threads: two
 //   radix-5 butterflies per thread and pass) and N2 = 600 (N' = 1200,
@@ -1039,8 +1263,8 @@ constexpr int kRowsPerBlock = 1 << kRowsShift;
 //   pitch axis: L = 1024 or 640 or 960 over 8 columns, L = 512 over 16
 //   columns.  A pitch block fills much of the LDS, so a CU holds two or three
 //   workgroups; they get 512 threads to keep enough waves.
-using TickCt3125 = FftCt<3125, kRowsShift, 3126, 1, 320, 5, 5, 5, 5, 5>;
-using TickCt600 = FftCt<600, kRowsShift, 601, 1, 128, 8, 5, 5, 3>;
+using TickCt3125 = FftCt<3125, 0, 3126, 1, 320, 5, 5, 5, 5, 5>;
+using TickCt600 = FftCt<600, 0, 601, 1, 128, 8, 5, 5, 3>;
 using PitchCt1024x8 = FftCt<1024, 3, 1, 8, 512, 16, 16, 4>;
 using PitchCt512x16 = FftCt<512, 4, 1, 16, 512, 8, 8, 8>;
 // Blocks a multiple of 10 rows long for the folded wire-output inverse, with
@@ -1058,24 +1282,27 @@ TwTables tick_tables(const wcsim_plane *pl)
 }
 
 // `blocks` = workgroups of the launch; a batch passes its total and tables.
-template <class FFT, bool B>
-void launch_r2c(const wcsim_plane *pl, FFT fft, int threads, const R2CIo &io,
-                const BatchTables &bt, unsigned blocks, hipStream_t s)
+size_t tick_lds(const wcsim_plane *pl, const TwTables &tw, int rows)
 {
-    const TwTables tw = tick_tables(pl);
-    const size_t lds = sizeof(float2) * ((size_t)(pl->N2 + 1) * kRowsPerBlock + tw.na + tw.nb);
-    hipLaunchKernelGGL((k_rows_r2c<FFT, B>), dim3(blocks), dim3(threads), lds, s, io, bt, pl->N2,
-                       fft, tw, ilog2(pl->F), pl->C, kRowsShift);
+    return sizeof(float2) * ((size_t)(pl->N2 + 1) * rows + tw.na + tw.nb);
 }
 
 template <class FFT, bool B>
-void launch_c2r(const wcsim_plane *pl, FFT fft, int threads, const C2RIo &io,
+void launch_r2c(const wcsim_plane *pl, FFT fft, dim3 threads, const R2CIo &io,
                 const BatchTables &bt, unsigned blocks, hipStream_t s)
 {
     const TwTables tw = tick_tables(pl);
-    const size_t lds = sizeof(float2) * ((size_t)(pl->N2 + 1) * kRowsPerBlock + tw.na + tw.nb);
-    hipLaunchKernelGGL((k_rows_c2r<FFT, B>), dim3(blocks), dim3(threads), lds, s, io, bt, pl->N2,
-                       fft, tw, ilog2(pl->F), pl->C, kRowsShift);
+    hipLaunchKernelGGL((k_rows_r2c<FFT, B>), dim3(blocks), threads, tick_lds(pl, tw, threads.y), s,
+                       io, bt, pl->N2, fft, tw, ilog2(pl->F), pl->C);
+}
+
+template <class FFT, bool B>
+void launch_c2r(const wcsim_plane *pl, FFT fft, dim3 threads, const C2RIo &io,
+                const BatchTables &bt, unsigned blocks, hipStream_t s)
+{
+    const TwTables tw = tick_tables(pl);
+    hipLaunchKernelGGL((k_rows_c2r<FFT, B>), dim3(blocks), threads, tick_lds(pl, tw, threads.y), s,
+                       io, bt, pl->N2, fft, tw, ilog2(pl->F), pl->C);
 }
 
 bool plan_is(const FftPlan &p, std::initializer_list<int> radices)
@@ -1099,10 +1326,40 @@ FftRt runtime_fft(const FftPlan &plan, int nseq_shift, int sstride, int estride)
     return f;
 }
 
-int tick_threads(const wcsim_plane *pl)
+// Plan of the general tick transform: among all ways to write n as radices
+// 16 .. 2, the fewest passes, then the fewest threads per row.  The first pass
+// (whose LDS stores are R values apart from lane to lane) takes an odd radix
+// where there is one: an even stride of 2 R words meets the same LDS banks
+// again after 32 / gcd(R, 32) lanes.
+void gen_search(int n, int maxr, std::vector<int> &cur, std::vector<int> &best, int &best_tx,
+                int total)
 {
-    return std::min(1024, std::max(256, threads_for(pl->planT, kRowsPerBlock)));
+    if (n == 1) {
+        int tx = 1;
+        for (int r : cur) {
+            const int per = gen_per_thread(r), nb = total / r;
+            tx = std::max(tx, (nb + per - 1) / per);
+        }
+        if (tx <= 1024 && (best.empty() || cur.size() < best.size() ||
+                           (cur.size() == best.size() && tx < best_tx))) {
+            best = cur;
+            best_tx = tx;
+        }
+        return;
+    }
+    if ((int)cur.size() == GenPlan::kMaxGen || (!best.empty() && cur.size() >= best.size()))
+        return;
+    for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2})
+        if (r <= maxr && n % r == 0) {
+            cur.push_back(r);
+            gen_search(n / r, r, cur, best, best_tx, total);
+            cur.pop_back();
+        }
 }
+
+// Planes of 6000 and 1000 ticks keep their compiled transforms.
+bool tick_is_3125(const wcsim_plane *pl) { return pl->N2 == 3125; }
+bool tick_is_600(const wcsim_plane *pl) { return pl->N2 == 600; }
 
 int pitch_threads(const wcsim_plane *pl)
 {
@@ -1113,13 +1370,13 @@ template <bool B>
 hipError_t rows_r2c_any(const wcsim_plane *pl, const R2CIo &io, const BatchTables &bt,
                         unsigned blocks, hipStream_t s)
 {
-    if (pl->N2 == 3125 && plan_is(pl->planT, {5, 5, 5, 5, 5}))
-        launch_r2c<TickCt3125, B>(pl, TickCt3125(), TickCt3125::kThreads, io, bt, blocks, s);
-    else if (pl->N2 == 600 && plan_is(pl->planT, {8, 5, 5, 3}))
-        launch_r2c<TickCt600, B>(pl, TickCt600(), TickCt600::kThreads, io, bt, blocks, s);
+    if (tick_is_3125(pl))
+        launch_r2c<TickCt3125, B>(pl, TickCt3125(), dim3(TickCt3125::kThreads), io, bt, blocks, s);
+    else if (tick_is_600(pl))
+        launch_r2c<TickCt600, B>(pl, TickCt600(), dim3(TickCt600::kThreads), io, bt, blocks, s);
     else
-        launch_r2c<FftRt, B>(pl, runtime_fft(pl->planT, kRowsShift, pl->N2 + 1, 1),
-                             tick_threads(pl), io, bt, blocks, s);
+        launch_r2c<FftGen, B>(pl, FftGen{pl->planG}, dim3(pl->tick_tx, pl->tick_rows), io, bt,
+                              blocks, s);
     return hipGetLastError();
 }
 
@@ -1127,29 +1384,28 @@ template <bool B>
 hipError_t rows_c2r_any(const wcsim_plane *pl, const C2RIo &io, const BatchTables &bt,
                         unsigned blocks, hipStream_t s)
 {
-    if (pl->N2 == 3125 && plan_is(pl->planT, {5, 5, 5, 5, 5}))
-        launch_c2r<TickCt3125, B>(pl, TickCt3125(), TickCt3125::kThreads, io, bt, blocks, s);
-    else if (pl->N2 == 600 && plan_is(pl->planT, {8, 5, 5, 3}))
-        launch_c2r<TickCt600, B>(pl, TickCt600(), TickCt600::kThreads, io, bt, blocks, s);
+    if (tick_is_3125(pl))
+        launch_c2r<TickCt3125, B>(pl, TickCt3125(), dim3(TickCt3125::kThreads), io, bt, blocks, s);
+    else if (tick_is_600(pl))
+        launch_c2r<TickCt600, B>(pl, TickCt600(), dim3(TickCt600::kThreads), io, bt, blocks, s);
     else
-        launch_c2r<FftRt, B>(pl, runtime_fft(pl->planT, kRowsShift, pl->N2 + 1, 1),
-                             tick_threads(pl), io, bt, blocks, s);
+        launch_c2r<FftGen, B>(pl, FftGen{pl->planG}, dim3(pl->tick_tx, pl->tick_rows), io, bt,
+                              blocks, s);
     return hipGetLastError();
 }
 
 hipError_t rows_r2c(const wcsim_plane *pl, const float *in, int nrows, int ncols,
                     int64_t in_stride, float2 *X, hipStream_t s, const uint8_t *occ = nullptr)
 {
-    static_assert(kOccRows % kRowsPerBlock == 0, "a tick-pass workgroup spans one map band");
     const R2CIo io = {in, nrows, ncols, in_stride, X, occ, occ ? occ_shift_of(ncols) : 0};
-    return rows_r2c_any<false>(pl, io, BatchTables{}, (unsigned)rows_blocks(nrows), s);
+    return rows_r2c_any<false>(pl, io, BatchTables{}, (unsigned)rows_blocks(pl, nrows), s);
 }
 
 hipError_t rows_c2r(const wcsim_plane *pl, const float2 *Y, int nrows, float *out, int ncols,
                     int64_t out_stride, hipStream_t s)
 {
     const C2RIo io = {Y, nrows, out, ncols, out_stride};
-    return rows_c2r_any<false>(pl, io, BatchTables{}, (unsigned)rows_blocks(nrows), s);
+    return rows_c2r_any<false>(pl, io, BatchTables{}, (unsigned)rows_blocks(pl, nrows), s);
 }
 
 template <class FFT, class FFT2, bool B>
@@ -1265,9 +1521,57 @@ int smallest_smooth_even(int nmin)
     }
 }
 
+// The general tick plan of a plane and the workgroup it runs in: rows of tx
+// threads, 1, 2, 4 or 8 of them -- whole wavefronts, at least three where rows
+// are short, and the fewest idle lanes; at most 512 threads and 40 KB of rows
+// beyond one, so that several workgroups share a CU.
+bool make_tick_plan(wcsim_plane *pl)
+{
+    const int n = pl->N2;
+    pl->tick_rows = 1;
+    if (tick_is_3125(pl) || tick_is_600(pl))
+        return true;
+    std::vector<int> cur, best;
+    int tx = 0;
+    gen_search(n, 16, cur, best, tx, n);
+    if (best.empty())
+        return false;
+    for (size_t k = 1; k < best.size() && best[0] % 2 == 0; ++k)
+        if (best[k] % 2 == 1)
+            std::swap(best[0], best[k]);
+    GenPlan &p = pl->planG;
+    p = GenPlan{};
+    p.n = n;
+    p.npass = (int)best.size();
+    int prod = 1;
+    for (int q = 0; q < p.npass; ++q) {
+        p.radix[q] = best[(size_t)q];
+        p.nb[q] = n / p.radix[q];
+        p.p[q] = prod;
+        p.tws[q] = n / (prod * p.radix[q]);
+        p.magic[q] = (uint32_t)((1ull << 32) / (uint64_t)prod + 1);
+        prod *= p.radix[q];
+    }
+    pl->tick_tx = (tx + 63) & ~63;
+    for (int r = 2; r <= 8; r *= 2) {
+        const int unit = 64 / r, t = (tx + unit - 1) / unit * unit;
+        if (t * r > 512 || sizeof(float2) * (size_t)(n + 1) * r > 40 * 1024)
+            break;
+        if (pl->tick_tx * pl->tick_rows < 192 || t < pl->tick_tx) {
+            pl->tick_rows = r;
+            pl->tick_tx = t;
+        }
+    }
+    return true;
+}
+
 int twiddle_table_len(int m) { return table_len(m); }
 
-int rows_blocks(int nrows) { return (nrows + kRowsPerBlock - 1) / kRowsPerBlock; }
+int rows_blocks(const wcsim_plane *pl, int nrows)
+{
+    const int r = pl->tick_rows;
+    return (nrows + r - 1) / r;
+}
 
 int pitch_blocks_total(const wcsim_plane *pl)
 {

@@ -132,6 +132,17 @@ struct FftPlan {
     int32_t radix[kMaxPass];
 };
 
+// Plan of a tick-axis transform of n points for run-time sizes.
+struct GenPlan {
+    static constexpr int kMaxGen = 8;
+    int32_t n, npass;
+    int32_t radix[kMaxGen];
+    int32_t nb[kMaxGen];      // n / radix: butterflies of the pass
+    int32_t p[kMaxGen];       // product of the earlier radices
+    int32_t tws[kMaxGen];     // n / (p radix): table step of the pass's factors
+    uint32_t magic[kMaxGen];  // floor(2^32 / p) + 1: i / p = mulhi(i, magic) for i, p < 2^16
+};
+
 bool make_plan(int n, FftPlan *plan);     // factor n into radices {8,4,2,5,3}
 int twiddle_table_len(int count);         // entries of a two-level twiddle table
 int smallest_smooth_even(int nmin);      // smallest even n >= nmin with n/2 plannable
@@ -163,6 +174,10 @@ struct wcsim_plane {
     bool fold;
     int Rp, Rt, r0;
     wcs::FftPlan planT, planL, planF;
+    // general tick-axis transform: plan, threads per row and rows per workgroup
+    // of passes A and C (one row for the lengths with a compiled transform)
+    wcs::GenPlan planG;
+    int tick_tx, tick_rows;
     float2 *twT;     // two-level table of exp(-2 pi i j / N2), j < N2
     float2 *twHalf;  // two-level table of exp(-2 pi i k / N'), k <= N2
     float2 *twL;     // two-level table of exp(-2 pi i j / L), j < L
@@ -288,7 +303,8 @@ hipError_t launch_convolve_batch_ab(const wcsim_plane *pl, const BatchTables &bt
                                     hipEvent_t after_a, hipEvent_t before_b);
 hipError_t launch_convolve_batch_c(const wcsim_plane *pl, const BatchTables &bt, int nblk_c,
                                    hipStream_t s);
-int rows_blocks(int nrows);                       // workgroups of a tick-axis pass
+int rows_blocks(const wcsim_plane *pl, int nrows);  // workgroups of a tick-axis pass
+bool make_tick_plan(wcsim_plane *pl);              // planG, tick_tx, tick_rows from N2
 int pitch_blocks_total(const wcsim_plane *pl);    // workgroups of the pitch pass
 int poly_blocks_total(const wcsim_plane *pl);     // workgroups of the polyphase pitch pass
 int poly_block_rows();                            // M, the polyphase block transform length
