@@ -237,3 +237,24 @@ def test_degenerate_depos_against_oracle(ws, det):
                 o, m = ometa[d, 4], ometa[d, 2] * ometa[d, 3]
                 if m and np.abs(ovals[o:o + m]).max() > 0:
                     assert normwise(vals[offs[d]:offs[d] + m], ovals[o:o + m]) <= GRID_TOL, (name, d)
+
+
+@pytest.mark.parametrize("det", [0, 1])
+def test_zero_charge_patches_across_the_grid_edge(ws, det):
+    """Patches whose draws are all zero keep their mean (zero here); of these
+    the first rows lie below the grid, so that the lanes holding the patches'
+    headers have no bin of their own to deposit.  The workspace holds NaN:
+    anything read beside a patch's own weights shows."""
+    pl = W.plane(20, 400)
+    rng = np.random.default_rng(45)
+    dep = W.uniform_depos(rng, 400, (-1.5, 0.5), (0.0, 200.0), max_drift_time=900.0)
+    dep[:, 4] = 0.0
+    P = ws.Plane(pl, W.physics(True), W.response("bipolar", Rp=21, Rt=40, r0=10), r0=10,
+                 schedule={"deterministic": det})
+    wsp = ws.simulate_workspace(P, 400, ws.OUT_PITCH)
+    wsp.fill_(0xFF)
+    out = ws.simulate_event(P, torch.from_numpy(dep).cuda(), 29, kind=ws.OUT_PITCH,
+                            workspace=wsp).cpu().numpy()
+    grid = ws.workspace_grid(P, wsp, 400).cpu().numpy()
+    assert np.abs(grid).max() == 0.0 and np.abs(out).max() == 0.0
+    P.destroy()
