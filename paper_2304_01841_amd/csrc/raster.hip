@@ -1307,37 +1307,35 @@ __device__ __forceinline__ void raster_item(float4 *acc4, double *xsum, const in
                 scale = (S > 0.0) ? (float)div_pos_d(pq, S) : -1.0f;
             }
             wave_lds_sync();  // the next batch may overwrite the prefix sums
+            // Rare: every fluctuated bin of a patch is zero.  The wavefront
+            // takes this branch together: the lane holding a patch's header may
+            // have no item of its own (a shuffle's source lane has to be active).
+            const bool mean = __any(scale < 0.0f);
 #pragma unroll
             for (int b = 0; b < kFluctItems; ++b) {
                 const float sc = __shfl(scale, kk[b], 64);
-                const bool live = b < npass && cell[b] >= 0;
-                if (live && sc >= 0.0f) {
-#pragma unroll
-                    for (int mm = 0; mm < 4; ++mm)
-                        F[b][mm] *= sc;
-                }
-                if (__any(live && sc < 0.0f)) {
-                    // rare: every fluctuated bin of a patch is zero.  The whole
-                    // wavefront takes this branch: the lane holding the patch's
-                    // header may have no such item (a source lane of a shuffle
-                    // has to be active).
+                if (mean) {
                     const int k = kk[b];
                     const int first = __shfl(incl - pitems, k, 64) - base;
                     const int m = __shfl(hdr.w, k, 64), nq = __shfl(pnq, k, 64);
                     const float q = __shfl(pqf, k, 64);
-                    if (live && sc < 0.0f) {
+                    if (b < npass && cell[b] >= 0 && sc < 0.0f) {
                         const int it = 64 * b + lane - first;
                         const int i = div_small(it, m);
                         const int qq = it - (int)__umul24(i, nq);
                         const float *rec = records + (int64_t)(beg + k) * kRecWords;
                         const float wp = rec[kRecWp + i];
                         const float4 wt = *(const float4 *)(rec + kRecWt + 4 * qq);
-                        F[b][0] = q * (wp * wt.x);
-                        F[b][1] = q * (wp * wt.y);
-                        F[b][2] = q * (wp * wt.z);
-                        F[b][3] = q * (wp * wt.w);
+                        F[b][0] = -(q * (wp * wt.x));
+                        F[b][1] = -(q * (wp * wt.y));
+                        F[b][2] = -(q * (wp * wt.z));
+                        F[b][3] = -(q * (wp * wt.w));
                     }
                 }
+                // (a scale of -1 turns the negated mean back)
+#pragma unroll
+                for (int mm = 0; mm < 4; ++mm)
+                    F[b][mm] *= sc;
             }
         }
         // Deposit, one patch of the batch at a time: the bins of one patch are
