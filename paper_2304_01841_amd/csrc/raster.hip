@@ -692,10 +692,14 @@ __global__ __launch_bounds__(256) void k_prep_bin(EventCtx e0, BatchTables bt, i
     }
 }
 
-// Tile schedule, two kernels over blocks of kSchedTiles tiles: per-tile depo
-// counts -> exclusive list offsets (in place, ntiles + 1 entries, the scan of
-// Sec. 4.3), and the list of work items {tile, first record, end record, 0}
-// of at most kChunk depos each.  counters[2] = number of work items.
+// Tile schedule over blocks of kSchedTiles tiles: per-tile depo counts -> list
+// offsets (in place) and the list of work items {tile, first record, end
+// record, 0} of at most kChunk depos each.  counters[2] = number of work items.
+// With float atomics (k_tile_schedule<false>) a block takes its place in both lists by
+// one atomic, so the lists hold the blocks in the order they came; one launch.
+// Reproducible sums need the lists in tile order (the scan of Sec. 4.3, ntiles +
+// 1 exclusive offsets): block totals, their scan, then the same pass; three
+// launches.  On the collection plane (225,000 tiles) 8.1 us against 16.8 us.
 constexpr int kSchedThreads = 256, kSchedPer = 16, kSchedTiles = kSchedThreads * kSchedPer;
 
 __device__ __forceinline__ int chunks_of(int count) { return (count + kChunk - 1) / kChunk; }
@@ -740,12 +744,16 @@ __global__ __launch_bounds__(kSchedThreads) void k_scan_block_tot(int2 *block_to
     }
 }
 
+// One block of tiles.  ORDERED: the block's bases come from the scanned totals;
+// otherwise from one 64-bit atomic on counters[2] (low word: work items) and
+// counters[3] (high word: depos), both below 2^31.
+template <bool ORDERED>
 __global__ __launch_bounds__(kSchedThreads) void k_tile_schedule(int32_t *tile_count, int ntiles,
                                                                 const int2 *block_base,
                                                                 int4 *items, int32_t *counters)
 {
     __shared__ int sh[kSchedThreads / 64];
-    const int base_t = block_base[blockIdx.x].x, base_c = block_base[blockIdx.x].y;
+    __shared__ unsigned long long place;
     const int first = blockIdx.x * kSchedTiles + threadIdx.x * kSchedPer;
     int cnt[kSchedPer];
     int st = 0, sc = 0;
@@ -757,12 +765,25 @@ __global__ __launch_bounds__(kSchedThreads) void k_tile_schedule(int32_t *tile_c
         sc += chunks_of(cnt[k]);
     }
     int tot_t, tot_c;
-    int off_t = block_exclusive_scan<int>(st, sh, &tot_t) + base_t;
-    int off_c = block_exclusive_scan<int>(sc, sh, &tot_c) + base_c;
+    int off_t = block_exclusive_scan<int>(st, sh, &tot_t);
+    int off_c = block_exclusive_scan<int>(sc, sh, &tot_c);
+    if (ORDERED) {
+        off_t += block_base[blockIdx.x].x;
+        off_c += block_base[blockIdx.x].y;
+    } else {
+        if (tot_t == 0)
+            return;  // no depo in the block: its offsets are never read
+        if (threadIdx.x == 0)
+            place = atomicAdd((unsigned long long *)(counters + 2),
+                              ((unsigned long long)(uint32_t)tot_t << 32) | (uint32_t)tot_c);
+        __syncthreads();
+        off_t += (int)(place >> 32);
+        off_c += (int)(uint32_t)place;
+    }
 #pragma unroll
     for (int k = 0; k < kSchedPer; ++k) {
         const int idx = first + k;
-        if (idx <= ntiles)
+        if (ORDERED ? idx <= ntiles : cnt[k] > 0)
             tile_count[idx] = off_t;
         const int nch = chunks_of(cnt[k]);
         for (int j = 0; j < nch; ++j) {
@@ -772,7 +793,7 @@ __global__ __launch_bounds__(kSchedThreads) void k_tile_schedule(int32_t *tile_c
         off_t += cnt[k];
         off_c += nch;
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kSchedThreads - 1)
+    if (ORDERED && blockIdx.x == gridDim.x - 1 && threadIdx.x == kSchedThreads - 1)
         counters[2] = off_c;
 }
 
@@ -2037,14 +2058,18 @@ static hipError_t raster_sequence(const wcsim_plane *pl, const EventCtx &e0,
     hipLaunchKernelGGL(k_prep_bin<B>, dim3(blocks_for(n, 256)), dim3(256), 0, s, e0, bt, n, g,
                        w.counters, w.tile_count, w.depo_tile, w.depo_slot, w.large);
     const unsigned sched_blocks = (unsigned)sched_blocks_of(ntiles);
-    hipLaunchKernelGGL(k_tile_sums, dim3(sched_blocks), dim3(kSchedThreads), 0, s, w.tile_count,
-                       (int)ntiles, w.block_tot);
-    hipLaunchKernelGGL(k_scan_block_tot, dim3(1), dim3(kSchedThreads), 0, s, w.block_tot,
-                       (int)sched_blocks);
-    hipLaunchKernelGGL(k_tile_schedule, dim3(sched_blocks), dim3(kSchedThreads), 0, s,
-                       w.tile_count, (int)ntiles, w.block_tot, w.items, w.counters);
-    if (pl->det)
+    if (pl->det) {
+        hipLaunchKernelGGL(k_tile_sums, dim3(sched_blocks), dim3(kSchedThreads), 0, s,
+                           w.tile_count, (int)ntiles, w.block_tot);
+        hipLaunchKernelGGL(k_scan_block_tot, dim3(1), dim3(kSchedThreads), 0, s, w.block_tot,
+                           (int)sched_blocks);
+        hipLaunchKernelGGL(k_tile_schedule<true>, dim3(sched_blocks), dim3(kSchedThreads), 0, s,
+                           w.tile_count, (int)ntiles, w.block_tot, w.items, w.counters);
         launch_tile_list_sort(n, ntiles, w, s);
+    } else {
+        hipLaunchKernelGGL(k_tile_schedule<false>, dim3(sched_blocks), dim3(kSchedThreads), 0, s,
+                           w.tile_count, (int)ntiles, w.block_tot, w.items, w.counters);
+    }
     // clearing blocks: one per band of grid rows, at most kMaxClearBlocks
     const int nclr = (int)std::min<int64_t>(kMaxClearBlocks, nbands);
     hipLaunchKernelGGL(k_fill_records<B>, dim3(blocks_for(n, 64) + nclr), dim3(128), 0, s, e0, bt,

@@ -244,8 +244,8 @@ hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *
 
 // fused raster + LDS-staged scatter
 struct RasterWork {
-    int32_t *counters;    // [0] invalid depos, [1] large-patch depos, [2] tile work items
-    int32_t *tile_count;  // [ntiles + 1] counts -> exclusive list offsets
+    int32_t *counters;    // [0] invalid depos, [1] large-patch depos, [2] tile work items, [3] listed
+    int32_t *tile_count;  // [ntiles + 1] counts -> list offsets of the tiles that hold depos
     int2 *block_tot;      // per schedule block: depos and work items
     int4 *items;          // work items {tile, first record, end record, 0}
     int32_t *depo_tile;   // [n] tile of each depo (-1: none)
