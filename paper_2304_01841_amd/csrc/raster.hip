@@ -1048,27 +1048,29 @@ static_assert(kHeaderWords <= kRecWp, "record header overflow");
 constexpr int kStageStride = kRecWords + 1;  // odd: one LDS bank per lane
 
 // Zero the blocks of one band of kOccRows grid rows whose bits are set in
-// `m` (bit c: ticks c 2^shift .. (c + 1) 2^shift - 1), by one wavefront.
+// `m` (bit c: ticks c 2^shift .. (c + 1) 2^shift - 1), by one wavefront.  A
+// block's row is a power of two of words long, so a lane's row and column are
+// shifts of its index (a division per store cost a fifth of this loop).
 __device__ __forceinline__ void clear_blocks(gptr<float> grid, int Np, int Nt, int band,
                                              uint64_t m, int shift, int lane)
 {
     const int r0 = band * kOccRows, nr = min(kOccRows, Np - r0);
+    const gptr<float> base = grid + (int64_t)r0 * Nt;
     while (m) {
-        const int c = __ffsll((unsigned long long)m) - 1;
+        const int c0 = (__ffsll((unsigned long long)m) - 1) << shift;
         m &= m - 1;
-        const int c0 = c << shift, c1 = min(c0 + (1 << shift), Nt);
         if ((Nt & 3) == 0) {  // rows of whole float4 words
-            const int nc = (c1 - c0) >> 2;
-            for (int i = lane; i < nr * nc; i += 64) {
-                const int r = i / nc;
-                *(gptr<float4>)(grid + (int64_t)(r0 + r) * Nt + c0 + 4 * (i - r * nc)) =
-                    make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            for (int i = lane; i < nr << (shift - 2); i += 64) {
+                const int r = i >> (shift - 2), c = c0 + 4 * (i & ((1 << (shift - 2)) - 1));
+                if (c < Nt)
+                    *(gptr<float4>)(base + (int64_t)r * Nt + c) =
+                        make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
         } else {
-            const int nc = c1 - c0;
-            for (int i = lane; i < nr * nc; i += 64) {
-                const int r = i / nc;
-                grid[(int64_t)(r0 + r) * Nt + c0 + (i - r * nc)] = 0.0f;
+            for (int i = lane; i < nr << shift; i += 64) {
+                const int r = i >> shift, c = c0 + (i & ((1 << shift) - 1));
+                if (c < Nt)
+                    base[(int64_t)r * Nt + c] = 0.0f;
             }
         }
     }
@@ -1079,24 +1081,26 @@ __device__ __forceinline__ void clear_blocks(gptr<float> grid, int Np, int Nt, i
 // weights (two FP64 chains per depo in flight instead of one, for the same
 // LDS), then the block writes the records out one 256-byte row at a time.
 // The first `nclr` blocks instead clear the occupied blocks of the grids, one
-// band of kOccRows rows per wavefront at a time (nbands bands over all
-// events): the clear is bound by HBM writes and the records by FP64
+// part of a band of kOccRows rows per wavefront at a time (nbands bands over
+// all events): the clear is bound by HBM writes and the records by FP64
 // arithmetic, so one launch runs both side by side.
 template <bool B>
 __global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables bt, int64_t ntotal,
                                                      const int32_t *depo_tile,
                                                      const int32_t *depo_slot,
                                                      const int32_t *tile_off, float *records,
-                                                     int nbands, int nclr)
+                                                     int nbands, int nclr, int parts_shift)
 {
     __shared__ float stage[64 * kStageStride];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if ((int)blockIdx.x < nclr) {
-        for (int gb = 2 * blockIdx.x + wv; gb < nbands; gb += 2 * nclr) {
+        for (int u = 2 * blockIdx.x + wv; u < nbands << parts_shift; u += 2 * nclr) {
+            const int gb = u >> parts_shift, part = u & ((1 << parts_shift) - 1);
             const int e = B ? find_event(bt.band_base, bt.nev, gb) : 0;
             const EventCtx &E = B ? bt.ev[e] : e0;
             const int band = B ? gb - bt.band_base[e] : gb;
-            const uint64_t m = __ballot(glb(E.occ)[band * kOccCols + lane] != 0);
+            const bool mine = (lane >> (6 - parts_shift)) == part;
+            const uint64_t m = __ballot(mine && glb(E.occ)[band * kOccCols + lane] != 0);
             clear_blocks(glb(E.grid), E.kp.Np, E.kp.Nt, band, m, E.occ_shift, lane);
         }
         return;
@@ -1830,9 +1834,16 @@ hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *
     return hipGetLastError();
 }
 
-// Blocks of the record kernel that clear the occupied blocks of the grids:
-// one per band of grid rows (300 for a 9600-row plane), at most this many.
+// Blocks of the record kernel that clear the occupied blocks of the grids: one
+// wavefront per part of a band of grid rows, at most kMaxClearBlocks blocks.
+// Bands are cut into 2^shift parts of map columns until kClearWaves wavefronts
+// share the clear: one wavefront took 110 us over a whole band of a long odd
+// readout (dword stores) and set the kernel's time.  333 wires x 4097 ticks: 120
+// us with whole bands, 53 with 256 wavefronts, 41 with 512 or 1024; 960 wires x
+// 6000 ticks: 72 us before, 68 with 256 or 512, 71 with 1024 (the clearing blocks
+// hold the LDS of record blocks).
 constexpr int kMaxClearBlocks = 4096;
+constexpr int kClearWaves = 512;
 
 static size_t sched_blocks_of(int64_t ntiles)
 {
@@ -2070,10 +2081,14 @@ static hipError_t raster_sequence(const wcsim_plane *pl, const EventCtx &e0,
         hipLaunchKernelGGL(k_tile_schedule<false>, dim3(sched_blocks), dim3(kSchedThreads), 0, s,
                            w.tile_count, (int)ntiles, w.block_tot, w.items, w.counters);
     }
-    // clearing blocks: one per band of grid rows, at most kMaxClearBlocks
-    const int nclr = (int)std::min<int64_t>(kMaxClearBlocks, nbands);
+    int parts_shift = 0;
+    while (parts_shift < 3 && (nbands << parts_shift) < kClearWaves)
+        ++parts_shift;
+    const int nclr =
+        (int)std::min<int64_t>(kMaxClearBlocks, ((nbands << parts_shift) + 1) / 2);
     hipLaunchKernelGGL(k_fill_records<B>, dim3(blocks_for(n, 64) + nclr), dim3(128), 0, s, e0, bt,
-                       n, w.depo_tile, w.depo_slot, w.tile_count, w.records, (int)nbands, nclr);
+                       n, w.depo_tile, w.depo_slot, w.tile_count, w.records, (int)nbands, nclr,
+                       parts_shift);
     if ((e = hipGetLastError()) != hipSuccess || (e = mark(0)) != hipSuccess)
         return e;
     const unsigned grid_items = raster_grid(ntiles, n);
