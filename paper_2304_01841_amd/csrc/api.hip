@@ -589,7 +589,8 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     if ((e = hipMalloc((void **)&P->meta, sizeof(int32_t) * 4 * nn)) != hipSuccess ||
         (e = hipMalloc((void **)&P->offsets, sizeof(int64_t) * (nn + 1))) != hipSuccess ||
-        (e = hipMalloc(&scratch, scan_scratch_bytes(n + 1))) != hipSuccess)
+        (e = hipMalloc(&scratch, scan_scratch_bytes(n + 1) + sizeof(int32_t) * (nn + 1))) !=
+            hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch set)"));
     const wcsim_depo *dd = depos;
     if (mem == WCSIM_MEM_HOST && n > 0) {
@@ -612,7 +613,8 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
     if ((e = hipMalloc((void **)&P->values, sizeof(float) * (size_t)std::max<int64_t>(total, 1))) !=
         hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch values)"));
-    if ((e = launch_patch_values(pl, dd, n, event_id, P->meta, P->offsets, P->values, s)) !=
+    if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values,
+                                 (int32_t *)((char *)scratch + scan_scratch_bytes(n + 1)), s)) !=
         hipSuccess)
         return bail(check_hip(e, "patch values"));
     if ((e = hipStreamSynchronize(s)) != hipSuccess)

@@ -235,9 +235,10 @@ hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, in
 size_t scan_scratch_bytes(int64_t n);
 hipError_t launch_exclusive_scan_i64(int64_t *data, int64_t n, void *scratch, hipStream_t s);
 hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hipStream_t s);
+// `list`: n + 1 words of scratch (the patches too large for a wavefront)
 hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
-                               uint64_t event_id, const int32_t *meta, const int64_t *offsets,
-                               float *values, hipStream_t s);
+                               uint64_t event_id, const int64_t *offsets, float *values,
+                               int32_t *list, hipStream_t s);
 hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *meta,
                                const int64_t *offsets, const float *values, float *grid,
                                hipStream_t s);
