@@ -33,6 +33,63 @@ struct wcs_spectrum {
     }
 };
 
+wcs_patch_buffers::~wcs_patch_buffers()
+{
+    for (Buffer &b : kept)
+        (void)hipFree(b.ptr);
+}
+
+// A kept buffer of the current device that is large enough, but not four times
+// too large, else a new one (once more without the kept ones when memory is out).
+hipError_t wcs_patch_buffers::take(int kind, size_t bytes, Buffer *out)
+{
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return e;
+    {
+        std::lock_guard<std::mutex> hold(lock);
+        Buffer &k = kept[kind];
+        if (k.ptr && k.device == dev && k.bytes >= bytes && k.bytes / 4 <= bytes) {
+            *out = k;
+            k = Buffer{};
+            return hipSuccess;
+        }
+    }
+    *out = Buffer{};
+    e = hipMalloc(&out->ptr, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        std::lock_guard<std::mutex> hold(lock);
+        for (Buffer &b : kept) {
+            (void)hipFree(b.ptr);
+            b = Buffer{};
+        }
+        e = hipMalloc(&out->ptr, bytes);
+    }
+    if (e != hipSuccess) {
+        *out = Buffer{};
+        return e;
+    }
+    out->bytes = bytes;
+    out->device = dev;
+    return hipSuccess;
+}
+
+void wcs_patch_buffers::give(int kind, Buffer *b)
+{
+    Buffer old = *b;
+    *b = Buffer{};
+    int dev = -1;
+    // (the synchronised device is the current one; hipFree waits for another)
+    if (old.ptr && old.bytes <= kMaxBytes && hipGetDevice(&dev) == hipSuccess &&
+        dev == old.device) {
+        std::lock_guard<std::mutex> hold(lock);
+        std::swap(old, kept[kind]);  // the newest stays: sets of one plane are of a size
+    }
+    (void)hipFree(old.ptr);
+}
+
 namespace wcs {
 
 namespace {
@@ -256,6 +313,7 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     wcsim_plane *pl = new (std::nothrow) wcsim_plane();
     if (!pl)
         return fail(WCSIM_E_NOMEM, "host allocation failed");
+    pl->patch_buffers = std::make_shared<wcs_patch_buffers>();
     pl->desc = *desc;
     pl->desc.response = nullptr;
     pl->phys = *phys;
@@ -569,37 +627,37 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
         return fail(WCSIM_E_NOMEM, "host allocation failed");
     P->n = n;
     P->device = pl->device;
-    void *scratch = nullptr;
+    P->buffers = pl->patch_buffers;
     auto bail = [&](wcsim_status r) {
-        (void)hipFree(scratch);
-        if (r != WCSIM_OK) {
-            (void)hipFree(P->meta);
-            (void)hipFree(P->offsets);
-            (void)hipFree(P->values);
-            (void)hipFree(P->staged);
-            delete P;
-        } else {
-            (void)hipFree(P->staged);
-            P->staged = nullptr;
+        if (r != WCSIM_OK)
+            wcsim_patches_destroy(P);
+        else
             *out = P;
-        }
         return r;
     };
     hipError_t e;
+    // one buffer: windows | offsets | scan scratch | list of large patches |
+    // device copy of host depos
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
-    if ((e = hipMalloc((void **)&P->meta, sizeof(int32_t) * 4 * nn)) != hipSuccess ||
-        (e = hipMalloc((void **)&P->offsets, sizeof(int64_t) * (nn + 1))) != hipSuccess ||
-        (e = hipMalloc(&scratch, scan_scratch_bytes(n + 1) + sizeof(int32_t) * (nn + 1))) !=
-            hipSuccess)
+    const size_t off_offs = align_up(sizeof(int32_t) * 4 * nn);
+    const size_t off_scan = off_offs + align_up(sizeof(int64_t) * (nn + 1));
+    const size_t off_list = off_scan + align_up(scan_scratch_bytes(n + 1));
+    const size_t off_depos = off_list + align_up(sizeof(int32_t) * (nn + 1));
+    const size_t bytes = off_depos + (mem == WCSIM_MEM_HOST ? sizeof(wcsim_depo) * nn : 0);
+    if ((e = P->buffers->take(0, bytes, &P->buf[0])) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch set)"));
+    char *base = (char *)P->buf[0].ptr;
+    P->meta = (int32_t *)base;
+    P->offsets = (int64_t *)(base + off_offs);
+    void *scratch = base + off_scan;
+    int32_t *list = (int32_t *)(base + off_list);
     const wcsim_depo *dd = depos;
     if (mem == WCSIM_MEM_HOST && n > 0) {
-        if ((e = hipMalloc((void **)&P->staged, sizeof(wcsim_depo) * nn)) != hipSuccess)
-            return bail(check_hip(e, "hipMalloc(depos)"));
-        if ((e = hipMemcpyAsync(P->staged, depos, sizeof(wcsim_depo) * (size_t)n,
+        wcsim_depo *staged = (wcsim_depo *)(base + off_depos);
+        if ((e = hipMemcpyAsync(staged, depos, sizeof(wcsim_depo) * (size_t)n,
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
             return bail(check_hip(e, "hipMemcpyAsync(depos)"));
-        dd = P->staged;
+        dd = staged;
     }
     if ((e = launch_patch_sizes(pl, dd, n, P->meta, P->offsets, s)) != hipSuccess ||
         (e = launch_exclusive_scan_i64(P->offsets, n + 1, scratch, s)) != hipSuccess)
@@ -610,12 +668,11 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "patch total"));
     P->nvalues = total;
-    if ((e = hipMalloc((void **)&P->values, sizeof(float) * (size_t)std::max<int64_t>(total, 1))) !=
-        hipSuccess)
+    if ((e = P->buffers->take(1, sizeof(float) * (size_t)std::max<int64_t>(total, 1),
+                              &P->buf[1])) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch values)"));
-    if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values,
-                                 (int32_t *)((char *)scratch + scan_scratch_bytes(n + 1)), s)) !=
-        hipSuccess)
+    P->values = (float *)P->buf[1].ptr;
+    if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values, list, s)) != hipSuccess)
         return bail(check_hip(e, "patch values"));
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "hipStreamSynchronize"));
@@ -668,10 +725,8 @@ void wcsim_patches_destroy(wcsim_patches *P)
     if (!P)
         return;
     (void)hipDeviceSynchronize();
-    (void)hipFree(P->meta);
-    (void)hipFree(P->offsets);
-    (void)hipFree(P->values);
-    (void)hipFree(P->staged);
+    for (int k = 0; k < 2; ++k)
+        P->buffers->give(k, &P->buf[k]);
     delete P;
 }
 

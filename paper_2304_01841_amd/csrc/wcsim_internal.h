@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -157,6 +158,28 @@ TileShape tile_shape(int id);
 }  // namespace wcs
 
 // ---------------------------------------------------------------------------
+// Device buffers of destroyed patch sets, kept for the next one of the same
+// plane: an allocation and a release cost 0.1-0.5 ms each, more than the
+// kernels of a 100,000-depo set.  At most one buffer of each kind and kMaxBytes
+// each; shared by the plane and its patch sets, released with the last of them.
+// A buffer comes back only after its patch set's destruction has synchronised
+// the device, so whoever takes it next may use it on any stream.
+// ---------------------------------------------------------------------------
+struct wcs_patch_buffers {
+    static constexpr size_t kMaxBytes = (size_t)256 << 20;
+    struct Buffer {
+        void *ptr = nullptr;
+        size_t bytes = 0;
+        int device = -1;
+    };
+    std::mutex lock;
+    Buffer kept[2];  // [0] windows, offsets and scratch, [1] values
+    ~wcs_patch_buffers();
+    hipError_t take(int kind, size_t bytes, Buffer *out);
+    void give(int kind, Buffer *b);  // (device idle)
+};
+
+// ---------------------------------------------------------------------------
 // Plane object
 // ---------------------------------------------------------------------------
 struct wcsim_plane {
@@ -193,6 +216,7 @@ struct wcsim_plane {
     // owner of K and the twiddle tables; planes with the same response and
     // transform sizes share one
     std::shared_ptr<struct wcs_spectrum> spectrum;
+    std::shared_ptr<struct wcs_patch_buffers> patch_buffers;
     int tile;
     bool det;  // reproducible sums: sorted tile lists, owner flush, ordered large patches
     wcs::TileShape ts;
@@ -203,11 +227,12 @@ struct wcsim_plane {
 struct wcsim_patches {
     int64_t n;
     int64_t nvalues;
-    int32_t *meta;     // [n][4]
-    int64_t *offsets;  // [n+1]
-    float *values;
-    wcsim_depo *staged;  // device copy of host depos (owned) or nullptr
+    int32_t *meta;     // [n][4], in buf[0]
+    int64_t *offsets;  // [n+1], in buf[0]
+    float *values;     // buf[1]
     int device;
+    wcs_patch_buffers::Buffer buf[2];
+    std::shared_ptr<wcs_patch_buffers> buffers;
 };
 
 namespace wcs {

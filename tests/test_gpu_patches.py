@@ -74,3 +74,62 @@ def test_windows_around_a_wavefronts_reach(fluct):
     edges = ometa[:, 2] + ometa[:, 3] + 2
     assert (edges > 64).sum() > 20 and (edges <= 64).sum() > 20
     _check(dep, phys, pl, 5, "mixed")
+
+
+def test_kept_buffers_serve_one_set_at_a_time():
+    """Sets of one plane made after others were destroyed: smaller, larger, two
+    alive together, host depos, several threads, and a set that outlives its
+    plane.  Every set holds its own values."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import threading
+    from paper_2304_01841_amd import wcsim
+    pl, phys = W.plane(12, 301), W.physics(True)
+    P = wcsim.Plane(pl, phys, W.response("unipolar", Rp=21, Rt=40, r0=10), r0=10)
+
+    def depos(seed, n):
+        return W.uniform_depos(np.random.default_rng(seed), n, (0.0, 60.0), (0.0, 150.0))
+
+    def same(pt, dep, ev):
+        meta, offs, vals = pt.to_host()
+        ometa, ovals, _ = O.rasterize(dep, phys, pl, ev)
+        assert np.array_equal(meta, ometa[:, :4]) and np.array_equal(offs[:-1], ometa[:, 4])
+        assert np.abs(vals - ovals).max() <= 1e-5 * ovals.max()
+
+    for n in (200, 150, 900, 20, 900):
+        dep = depos(n, n)
+        pt = wcsim.rasterize(P, dep if n == 150 else torch.from_numpy(dep).cuda(), n)
+        same(pt, dep, n)
+        pt.destroy()
+    a, b = depos(1, 300), depos(2, 280)
+    pa = wcsim.rasterize(P, torch.from_numpy(a).cuda(), 1)
+    pb = wcsim.rasterize(P, torch.from_numpy(b).cuda(), 2)
+    same(pa, a, 1)
+    same(pb, b, 2)
+    pa.destroy()
+    pb.destroy()
+    failed = []
+
+    def worker(seed):
+        try:
+            s = torch.cuda.Stream()
+            for r in range(4):
+                dep = depos(10 * seed + r, 100 + 30 * seed)
+                dd = torch.from_numpy(dep).cuda()
+                torch.cuda.current_stream().synchronize()
+                pt = wcsim.rasterize(P, dd, r, stream=s)
+                same(pt, dep, r)
+                pt.destroy()
+        except Exception as e:  # noqa: BLE001 (reported below)
+            failed.append(e)
+
+    ts = [threading.Thread(target=worker, args=(k,)) for k in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not failed, failed
+    last = wcsim.rasterize(P, torch.from_numpy(a).cuda(), 1)
+    P.destroy()
+    same(last, a, 1)
+    last.destroy()
