@@ -23,6 +23,7 @@
 // memory, and every global<->LDS copy issues its loads in batches.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -1331,30 +1332,30 @@ FftRt runtime_fft(const FftPlan &plan, int nseq_shift, int sstride, int estride)
 // (whose LDS stores are R values apart from lane to lane) takes an odd radix
 // where there is one: an even stride of 2 R words meets the same LDS banks
 // again after 32 / gcd(R, 32) lanes.
-void gen_search(int n, int maxr, std::vector<int> &cur, std::vector<int> &best, int &best_tx,
-                int total)
+//
+// Non-increasing radices of exactly `left` more passes for the rest m of n; tx:
+// threads a row of the passes so far.
+void gen_search(int n, int m, int maxr, int left, int tx, int *cur, int *best, int *best_tx)
 {
-    if (n == 1) {
-        int tx = 1;
-        for (int r : cur) {
-            const int per = gen_per_thread(r), nb = total / r;
-            tx = std::max(tx, (nb + per - 1) / per);
-        }
-        if (tx <= 1024 && (best.empty() || cur.size() < best.size() ||
-                           (cur.size() == best.size() && tx < best_tx))) {
-            best = cur;
-            best_tx = tx;
+    if (left == 0) {
+        if (m == 1 && tx < *best_tx) {
+            std::copy(cur, cur + GenPlan::kMaxGen, best);
+            *best_tx = tx;
         }
         return;
     }
-    if ((int)cur.size() == GenPlan::kMaxGen || (!best.empty() && cur.size() >= best.size()))
+    int64_t most = 1;  // what `left` radices can still make up
+    for (int k = 0; k < left; ++k)
+        most *= maxr;
+    if (m > most)
         return;
-    for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2})
-        if (r <= maxr && n % r == 0) {
-            cur.push_back(r);
-            gen_search(n / r, r, cur, best, best_tx, total);
-            cur.pop_back();
-        }
+    for (int r : {16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2}) {
+        const int per = gen_per_thread(r), need = (n / r + per - 1) / per;
+        if (r > maxr || m % r != 0 || std::max(tx, need) >= *best_tx)
+            continue;
+        cur[left - 1] = r;
+        gen_search(n, m / r, r, left - 1, std::max(tx, need), cur, best, best_tx);
+    }
 }
 
 // Planes of 6000 and 1000 ticks keep their compiled transforms.
@@ -1531,21 +1532,23 @@ bool make_tick_plan(wcsim_plane *pl)
     pl->tick_rows = 1;
     if (tick_is_3125(pl) || tick_is_600(pl))
         return true;
-    std::vector<int> cur, best;
-    int tx = 0;
-    gen_search(n, 16, cur, best, tx, n);
-    if (best.empty())
-        return false;
-    for (size_t k = 1; k < best.size() && best[0] % 2 == 0; ++k)
+    int cur[GenPlan::kMaxGen] = {}, best[GenPlan::kMaxGen] = {}, tx = 1025, npass = 0;
+    while (tx > 1024) {
+        if (++npass > GenPlan::kMaxGen)
+            return false;
+        gen_search(n, n, 16, npass, 1, cur, best, &tx);
+    }
+    std::reverse(best, best + npass);  // largest first
+    for (int k = 1; k < npass && best[0] % 2 == 0; ++k)
         if (best[k] % 2 == 1)
             std::swap(best[0], best[k]);
     GenPlan &p = pl->planG;
     p = GenPlan{};
     p.n = n;
-    p.npass = (int)best.size();
+    p.npass = npass;
     int prod = 1;
     for (int q = 0; q < p.npass; ++q) {
-        p.radix[q] = best[(size_t)q];
+        p.radix[q] = best[q];
         p.nb[q] = n / p.radix[q];
         p.p[q] = prod;
         p.tws[q] = n / (prod * p.radix[q]);
