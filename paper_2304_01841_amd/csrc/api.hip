@@ -220,14 +220,14 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc)
     int L = (sc && sc->fft_pitch) ? sc->fft_pitch
                                   : std::min(2048, std::max(256, pow2_at_least(4 * pl->Rp)));
     // Default chunk with long pitch blocks: 16 columns when the tick spectrum of
-    // the grid exceeds 96 MiB, else 8.  Sixteen make whole 128-byte lines of each
+    // the grid exceeds 64 MiB, else 8.  Sixteen make whole 128-byte lines of each
     // pitch row (with 8 the two halves of a line are written and read by
     // workgroups of different L2s, which costs once the spectrum goes out to
     // HBM); eight give the pitch passes twice the workgroups.  Wire output, 8 / 16
-    // columns: 960 wires x 6000 ticks 231 / 196 us, 480 x 6000 (115 MiB) 128 / 118,
-    // 300 x 9000 (105 MiB) 133 / 123, 200 x 9000 (70 MiB) 87 / 86, 300 x 6000
-    // (72 MiB) 74 / 76, 480 x 3000 (59 MiB) 81 / 83, 100 x 4096 48 / 51.
-    const bool long_lines = sizeof(float2) * (size_t)pl->Np * (pl->N2 + 1) > ((size_t)96 << 20);
+    // columns: 960 wires x 6000 ticks 231 / 196 us, 480 x 6000 (115 MiB) 127 / 109,
+    // 300 x 6000 (72 MiB) 71 / 67, 480 x 3000 (59 MiB) 77 / 78, 100 x 6000 (24 MiB)
+    // 41.3 / 41.4, 300 x 1000 28.6 / 32.4.
+    const bool long_lines = sizeof(float2) * (size_t)pl->Np * (pl->N2 + 1) > ((size_t)64 << 20);
     pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && !long_lines ? 8 : 16);
     if (pl->F != 8 && pl->F != 16)
         return fail(WCSIM_E_INVALID, "freq_chunk must be 8 or 16");

@@ -399,7 +399,8 @@ struct HasPrefetch<S, std::void_t<decltype(&S::prefetch)>> : std::true_type {};
 
 template <int N, int R, int P, int NSS, int SS, int ES, int NT, bool GLOAD, bool GSTORE,
           class Load, class Store>
-__device__ __forceinline__ void ct_pass(float2 *buf, const float2 *tab, Load &load, Store &store)
+__device__ __forceinline__ void ct_pass(float2 *buf, const float2 *tab, Load &load, Store &store,
+                                        const int tid)
 {
     constexpr int NB = N / R;
     constexpr int TOTAL = NB << NSS;
@@ -409,7 +410,6 @@ __device__ __forceinline__ void ct_pass(float2 *buf, const float2 *tab, Load &lo
     // Unguarded loads when at most 1/8 of them would be discarded.
     constexpr bool kLoadAll = 8 * (MAXB * NT - TOTAL) <= MAXB * NT;
     static_assert(!GLOAD || P == 1, "only the first pass reads its inputs from a loader");
-    const int tid = threadIdx.x;
     float2 v[MAXB][R];
 #pragma unroll
     for (int b = 0; b < MAXB; ++b) {
@@ -485,14 +485,15 @@ __device__ __forceinline__ void ct_pass(float2 *buf, const float2 *tab, Load &lo
 
 template <int N, int NSS, int SS, int ES, int NT, int P, class Load, class Store, int R,
           int... Rest>
-__device__ __forceinline__ void ct_fft(float2 *buf, const float2 *tab, Load &load, Store &store)
+__device__ __forceinline__ void ct_fft(float2 *buf, const float2 *tab, Load &load, Store &store,
+                                       const int tid)
 {
     constexpr bool kLast = sizeof...(Rest) == 0;
     constexpr bool kLoad = P == 1 && !std::is_same<Load, InLds>::value;
     constexpr bool kStore = kLast && !std::is_same<Store, InLds>::value;
-    ct_pass<N, R, P, NSS, SS, ES, NT, kLoad, kStore>(buf, tab, load, store);
+    ct_pass<N, R, P, NSS, SS, ES, NT, kLoad, kStore>(buf, tab, load, store, tid);
     if constexpr (!kLast)
-        ct_fft<N, NSS, SS, ES, NT, P * R, Load, Store, Rest...>(buf, tab, load, store);
+        ct_fft<N, NSS, SS, ES, NT, P * R, Load, Store, Rest...>(buf, tab, load, store, tid);
 }
 
 // Compile-time transform as a policy object.  run(): LDS in, LDS out.
@@ -505,13 +506,13 @@ struct FftCt {
     __device__ __forceinline__ void run(float2 *buf, const float2 *tab) const
     {
         InLds in, out;
-        ct_fft<N, NSS, SS, ES, NT, 1, InLds, InLds, Rs...>(buf, tab, in, out);
+        ct_fft<N, NSS, SS, ES, NT, 1, InLds, InLds, Rs...>(buf, tab, in, out, threadIdx.x);
     }
     template <class Load, class Store>
     __device__ __forceinline__ void run_io(float2 *buf, const float2 *tab, Load load,
                                            Store store) const
     {
-        ct_fft<N, NSS, SS, ES, NT, 1, Load, Store, Rs...>(buf, tab, load, store);
+        ct_fft<N, NSS, SS, ES, NT, 1, Load, Store, Rs...>(buf, tab, load, store, threadIdx.x);
     }
 };
 
@@ -1115,6 +1116,11 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_pitch_conv(PitchIo io, Bat
 // every phase) are multiplied by H_b and summed in registers; then the inverse
 // (a forward transform of the conjugate).  Workgroups are mapped XCD-major as
 // in k_pitch_conv.
+// A phase is a chain of a global load, two passes and two barriers (about 2 us),
+// and a workgroup runs its D phases in series.  Launches of too few workgroups
+// to fill the chip cut the phases over S groups of 8 F threads, each with its own
+// LDS block and sum; the groups' spectra are then added, and every group runs the
+// inverse (so that all meet its barriers), the first one storing it.
 // ---------------------------------------------------------------------------
 constexpr int kPolyM = 128;
 constexpr int kPolyMaxTaps = 64;  // A <= 64: at least 65 wires per block
@@ -1126,14 +1132,16 @@ struct PolyIo {
     int Nw, nblocks;
 };
 
-template <int F, bool BATCH>
-__global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt, int C, int D,
-                                                      int A, int cw, const float2 *twM)
+template <int F, int S, bool BATCH>
+__global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables bt, int C, int D,
+                                                          int A, int cw, const float2 *twM)
 {
     constexpr int NT = 8 * F, M = kPolyM, NSS = (F == 16) ? 4 : 3;
     constexpr int NTAB = kTwLo + M / kTwLo + 1;  // two-level table of exp(-2 pi i j / M)
-    __shared__ float2 buf[M * F];
+    __shared__ float2 bufs[S][M * F];
     __shared__ float2 tab[NTAB];
+    const int grp = (S > 1) ? (int)threadIdx.x / NT : 0;
+    float2 *buf = bufs[grp];
     int gblk = blockIdx.x;
     if (BATCH) {
         const int e = find_event(bt.pblk_base, bt.nev, gblk);
@@ -1151,10 +1159,11 @@ __global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt,
     const int c = lc * 8 + xcd;
     if (c >= C)
         return;
-    for (int t = threadIdx.x; t < NTAB; t += NT)
+    for (int t = threadIdx.x; t < NTAB; t += S * NT)
         tab[t] = twM[t];
     const int V = M - A + 1, w0 = blk * V;
-    const int tid = threadIdx.x, s = tid % F, i = tid / F;  // radix-16 butterfly i < 8 of column s
+    const int tid = threadIdx.x - grp * NT;
+    const int s = tid % F, i = tid / F;  // radix-16 butterfly i < 8 of column s
     const gptr<const float2> Xc = glb(io.X) + (int64_t)c * io.Np * F;
     const gptr<const float2> Hc = glb(io.H) + (int64_t)c * D * M * F;
     float2 acc[16];
@@ -1162,7 +1171,8 @@ __global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt,
     for (int t = 0; t < 16; ++t)
         acc[t] = make_float2(0.0f, 0.0f);
     InLds none;
-    for (int b = 0; b < D; ++b) {
+    for (int b0 = 0; b0 < D; b0 += S) {
+        const int b = (S > 1) ? min(b0 + grp, D - 1) : b0;  // (a surplus phase is not added)
         const int phi = ((cw - b) % D + D) % D;
         const int m0 = w0 + (cw - b - phi) / D - (A - 1);
         // x_b[j] from global memory (zero outside the grid), from a clamped row
@@ -1172,7 +1182,7 @@ __global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt,
             const float2 v = Xc[(int64_t)qc * F + col];
             return (q == qc) ? v : make_float2(0.0f, 0.0f);
         };
-        ct_pass<M, 8, 1, NSS, 1, F, NT, true, false>(buf, tab, load, none);
+        ct_pass<M, 8, 1, NSS, 1, F, NT, true, false>(buf, tab, load, none, tid);
         // radix-16 pass (p = 8) into registers, then times H_b, summed over b
         const gptr<const float2> Hb = Hc + (int64_t)b * M * F;
         float2 h[16], v[16];
@@ -1184,10 +1194,26 @@ __global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt,
             v[t] = buf[(i + 8 * t) * F + s];
         twiddle_powers<16>(v, tw_at(tab, i));
         dft<16>(v);
+        if (S == 1 || b0 + grp < D) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t)
+                acc[t] = cadd(acc[t], cmul(v[t], h[t]));
+        }
+        __syncthreads();  // every read of this phase precedes the next phase's writes
+    }
+    if constexpr (S > 1) {
 #pragma unroll
         for (int t = 0; t < 16; ++t)
-            acc[t] = cadd(acc[t], cmul(v[t], h[t]));
-        __syncthreads();  // every read of this phase precedes the next phase's writes
+            buf[(i + 8 * t) * F + s] = acc[t];
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            acc[t] = bufs[0][(i + 8 * t) * F + s];
+#pragma unroll
+            for (int g = 1; g < S; ++g)
+                acc[t] = cadd(acc[t], bufs[g][(i + 8 * t) * F + s]);
+        }
+        __syncthreads();
     }
     // inverse: the forward transform of the conjugate, conjugated
 #pragma unroll
@@ -1198,11 +1224,11 @@ __global__ __launch_bounds__(8 * F) void k_pitch_poly(PolyIo io, BatchTables bt,
     const int nw = io.Nw;
     auto store = [&](int col, int j, float2 val) {
         const int w = w0 + j - (A - 1);
-        if (j < A - 1 || w >= nw)
+        if (j < A - 1 || w >= nw || grp != 0)
             return;
         Yc[(int64_t)w * F + col] = conjf2(val);
     };
-    ct_fft<M, NSS, 1, F, NT, 1, InLds, decltype(store), 8, 16>(buf, tab, none, store);
+    ct_fft<M, NSS, 1, F, NT, 1, InLds, decltype(store), 8, 16>(buf, tab, none, store, tid);
 }
 
 // Response spectra of the polyphase pass: H[c][b][f][s] = sum_{a < A, D a + b < Rp}
@@ -1596,17 +1622,36 @@ int poly_blocks_total(const wcsim_plane *pl)
     return 8 * ((pl->C + 7) / 8) * pl->polyBlocks;
 }
 
-// The polyphase pitch pass of one plane (io set) or of a batch (tables).
+template <int F, int S, bool B>
+void launch_poly(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt, unsigned blocks,
+                 hipStream_t s)
+{
+    hipLaunchKernelGGL((k_pitch_poly<F, S, B>), dim3(blocks), dim3(8 * F * S), 0, s, io, bt, pl->C,
+                       (int)pl->kp.nimpact, pl->polyA, pl->polyCw, pl->twP);
+}
+
+// The polyphase pitch pass of one plane (io set) or of a batch (tables).  The
+// phases are cut over five groups while the launch has at most one wavefront per
+// CU without, over two while it then has at most 16 per CU (what 124 registers
+// leave room for).  Convolution, wire output, with one group / so: 100 wires x 1000
+// ticks 34.3 / 22.0 us, 200 x 2000 (1.1 wavefronts a CU) 50.3 / 41.7 (five groups
+// 45.4), 200 x 6000 (3.1) 61.5 / 53.6 (five 73.1), 480 x 6000 (7.8) 116.8 / 109.4,
+// 800 x 6000 (12.5: one group).  A plane of reproducible sums keeps one group, so
+// that its sums do not depend on what shares the launch.
 template <bool B>
 hipError_t poly_any(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt,
                     unsigned blocks, hipStream_t s)
 {
+    const unsigned waves = blocks * (unsigned)pl->F / 8, cus = 256;
+    const int S = (pl->det || 2 * waves > 16 * cus) ? 1 : (waves > cus) ? 2 : 5;
     if (pl->F == 16)
-        hipLaunchKernelGGL((k_pitch_poly<16, B>), dim3(blocks), dim3(128), 0, s, io, bt, pl->C,
-                           (int)pl->kp.nimpact, pl->polyA, pl->polyCw, pl->twP);
+        S == 1   ? launch_poly<16, 1, B>(pl, io, bt, blocks, s)
+        : S == 2 ? launch_poly<16, 2, B>(pl, io, bt, blocks, s)
+                 : launch_poly<16, 5, B>(pl, io, bt, blocks, s);
     else
-        hipLaunchKernelGGL((k_pitch_poly<8, B>), dim3(blocks), dim3(64), 0, s, io, bt, pl->C,
-                           (int)pl->kp.nimpact, pl->polyA, pl->polyCw, pl->twP);
+        S == 1   ? launch_poly<8, 1, B>(pl, io, bt, blocks, s)
+        : S == 2 ? launch_poly<8, 2, B>(pl, io, bt, blocks, s)
+                 : launch_poly<8, 5, B>(pl, io, bt, blocks, s);
     return hipGetLastError();
 }
 
