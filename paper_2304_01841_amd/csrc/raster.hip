@@ -294,6 +294,38 @@ __device__ __forceinline__ double wave_incl_scan_d(double v)
     return v;
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_shift_i(int v, int other)
+{
+    return __builtin_amdgcn_update_dpp(other, v, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive prefix sum of an integer, and the largest (MIN: smallest) integer of
+// the wavefront's lanes (uniform), by the same shifts: no LDS round trips.
+__device__ __forceinline__ int wave_incl_scan_i(int v)
+{
+    v += dpp_shift_i<0x111, 0xf>(v, 0);
+    v += dpp_shift_i<0x112, 0xf>(v, 0);
+    v += dpp_shift_i<0x114, 0xf>(v, 0);
+    v += dpp_shift_i<0x118, 0xf>(v, 0);
+    v += dpp_shift_i<0x142, 0xa>(v, 0);
+    v += dpp_shift_i<0x143, 0xc>(v, 0);
+    return v;
+}
+
+template <bool MIN>
+__device__ __forceinline__ int wave_max_i(int v)
+{
+    auto pick = [](int a, int b) { return MIN ? min(a, b) : max(a, b); };
+    v = pick(v, dpp_shift_i<0x111, 0xf>(v, v));
+    v = pick(v, dpp_shift_i<0x112, 0xf>(v, v));
+    v = pick(v, dpp_shift_i<0x114, 0xf>(v, v));
+    v = pick(v, dpp_shift_i<0x118, 0xf>(v, v));
+    v = pick(v, dpp_shift_i<0x142, 0xa>(v, v));
+    v = pick(v, dpp_shift_i<0x143, 0xc>(v, v));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 __device__ __forceinline__ double readlane_d(double v, int lane)
 {
     const long long b = __double_as_longlong(v);
@@ -1495,15 +1527,10 @@ __device__ __forceinline__ void raster_item(float4 *acc4, double *xsum, const in
     // Only the bounding box of the chunk's patches (in region rows and tick
     // quads, within the grid) is cleared and flushed; deposits outside the
     // grid land outside it and are never read.
-    int rlo = win.x, rhi = (win.z > 0) ? win.x + win.z : INT_MIN;
-    int qlo = quad_of(win.y), qhi = (win.z > 0) ? quad_of(win.y + win.w - 1) + 1 : INT_MIN;
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-        rlo = min(rlo, __shfl_xor(rlo, m, 64));
-        rhi = max(rhi, __shfl_xor(rhi, m, 64));
-        qlo = min(qlo, __shfl_xor(qlo, m, 64));
-        qhi = max(qhi, __shfl_xor(qhi, m, 64));
-    }
+    const int rlo = wave_max_i<true>(win.x);
+    const int rhi = wave_max_i<false>((win.z > 0) ? win.x + win.z : INT_MIN);
+    const int qlo = wave_max_i<true>(quad_of(win.y));
+    const int qhi = wave_max_i<false>((win.z > 0) ? quad_of(win.y + win.w - 1) + 1 : INT_MIN);
     const int br0 = max(rlo, p0) - p0;
     const int br1 = min(min(rhi, (int)P.Np), p0 + RP) - p0;
     const int bq0 = max(4 * max(qlo, 0) - c0, 0) >> 2;
@@ -1519,13 +1546,9 @@ __device__ __forceinline__ void raster_item(float4 *acc4, double *xsum, const in
     const int pqlo = quad_of(win.y);
     const int pnq = (lane < K) ? quad_of(win.y + win.w - 1) - pqlo + 1 : 0;
     const int pitems = (lane < K) ? win.z * pnq : 0;
-    int incl = pitems;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(incl, o, 64);
-        if (lane >= o)
-            incl += u;
-    }
+    const int incl = wave_incl_scan_i(pitems);
+    // records of the item: 32-bit offsets from here
+    const gptr<const float> item_rec = glb(records) + (int64_t)beg * kRecWords;
     const double pq = __longlong_as_double(
         (long long)(((uint64_t)(uint32_t)hdr.z << 32) | (uint32_t)hdr.y));  // patch charge, FP64
     const float pqf = (float)pq;
@@ -1575,14 +1598,18 @@ __device__ __forceinline__ void raster_item(float4 *acc4, double *xsum, const in
                 cell[b] = (valid && (unsigned)r < (unsigned)RP && (unsigned)c <= (unsigned)(RT - 4))
                               ? (r * RT + c) >> 2
                               : -1;
-                const float *rec = records + (int64_t)(beg + k) * kRecWords;
-                const float wp = valid ? rec[kRecWp + i] : 0.0f;
-                const float4 wt = *(const float4 *)(rec + kRecWt + 4 * qq);
+                // loaded by every lane (a surplus one reads its batch's last
+                // patch): a branch around the loads would make each pass wait
+                // for them before its Philox rounds
+                const float wpl = item_rec[(uint32_t)(k * kRecWords + kRecWp + i)];
+                const float4 wt =
+                    *(gptr<const float4>)(item_rec + (uint32_t)(k * kRecWords + kRecWt + 4 * qq));
                 const float w4[4] = {wt.x, wt.y, wt.z, wt.w};
                 if constexpr (FLUCT) {
                     const uint4 rr = philox4x32_10(
                         make_uint4((uint32_t)qd, (uint32_t)(lo_p + i), (uint32_t)d, E.event),
                         P.key0, P.key1);
+                    const float wp = valid ? wpl : 0.0f;
                     constexpr float kMinus2Ln2 = -1.38629436111989061883f;
                     const float r2a = kMinus2Ln2 * __builtin_amdgcn_logf(word_to_uniform(rr.x));
                     const float r2b = kMinus2Ln2 * __builtin_amdgcn_logf(word_to_uniform(rr.z));
@@ -1601,6 +1628,7 @@ __device__ __forceinline__ void raster_item(float4 *acc4, double *xsum, const in
                     xsum[g] = x;
                     carry = readlane_d(x, 63);
                 } else {
+                    const float wp = valid ? wpl : 0.0f;
 #pragma unroll
                     for (int mm = 0; mm < 4; ++mm)
                         F[b][mm] = q * (wp * w4[mm]);
