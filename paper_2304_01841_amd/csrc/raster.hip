@@ -1749,15 +1749,25 @@ __global__ __launch_bounds__(64) void k_raster_tiles(const float *__restrict__ r
 // Owner flush (reproducible sums).  Tiles are coloured by (tile row mod CP,
 // tile column mod CT), with CP TP >= RP and CT TT >= RT, so that the LDS
 // regions of two tiles of one colour never share a grid cell; one launch per
-// colour, in a fixed order.  In a launch each tile of the colour is owned by
-// one workgroup of kOwnerWaves wavefronts: wavefront w draws the tile's work
-// items w, w + kOwnerWaves, ... (in list order) into its own copy of the
-// region, and the workgroup adds the sum of the copies to the grid with plain
-// read-add-writes.  Every cell receives its sums in the same order on every
-// run.  The launch is persistent over the colour's list of tiles (the items
-// that open them), one workgroup per resident slot.
-constexpr int kOwnerWaves = 2;
-constexpr int kColourCount = 3, kColourNext = 9;  // counters: tiles per colour, places handed out
+// colour, in a fixed order.  In a launch each tile of the colour is owned by one
+// workgroup or one wavefront.  Light tiles (at most kLightItems work items) go to
+// a wavefront each, which draws their items one after another into its region and
+// adds the region to the grid with plain read-add-writes.  Heavy tiles -- a track
+// nearly along the wires leaves most of its 2,500 depos, 78 work items, in a few
+// tiles, and set the time of a phase -- go to a workgroup of kOwnerWaves
+// wavefronts: wavefront w draws items w, w + kOwnerWaves, ... into its own copy of
+// the region, and the workgroup adds the sum of the copies.  Every cell receives
+// its sums in the same order on every run.  The launch is persistent over the
+// colour's lists (the items that open the tiles), heavy tiles first.
+// Whole events, four sets of 150,000 track depos on 480 wires: 660-1490 us with
+// two wavefronts for every tile, 570-740 us so; 500,000 depos on 960 wires
+// 1310-2180 and 1100-1240 us.  (Two items a light tile: 670-890 us; eight
+// wavefronts a heavy one 570-680 and 1160-1250 us, four 570-900 and 1040-1340.)
+constexpr int kOwnerWaves = 6, kLightItems = 1;
+// counters: tiles per list, places handed out; lists: colour c's heavy tiles at
+// 2 c, its light tiles at 2 c + 1
+constexpr int kMaxColours = 9;
+constexpr int kColourCount = 4, kColourNext = kColourCount + 2 * kMaxColours;
 
 template <int TP, int TT>
 constexpr int owner_colours_p()
@@ -1770,15 +1780,15 @@ constexpr int owner_colours_t()
     return (region_cols<TT>() + TT - 1) / TT;
 }
 
-// Add a complete region to the grid (one workgroup of NT threads, exclusive
-// owner of the region's cells): quads wholly inside the grid as 16-byte
+// Add a complete region to the grid (NT threads, exclusive owners of the region's
+// cells): quads wholly inside the grid as 16-byte
 // read-add-writes when rows are whole float4 words, the others cell by cell.
 // The region is the sum of the NW wavefronts' copies, taken in wavefront
 // order.  Each thread's grid values are all loaded before any is stored, so
 // that the loads are in flight together.
 template <int RP, int RT, int NW, int NT>
 __device__ __forceinline__ void owner_flush(const float4 *acc4, gptr<float> grid, int Np, int Nt,
-                                            int p0, int c0)
+                                            int p0, int c0, int tid)
 {
     constexpr int RQ = RT / 4, NQ = (RP * RQ + NT - 1) / NT;
     const bool vec = (Nt & 3) == 0;
@@ -1787,7 +1797,7 @@ __device__ __forceinline__ void owner_flush(const float4 *acc4, gptr<float> grid
     bool whole[NQ], any[NQ];
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
-        const int x = threadIdx.x + NT * u;
+        const int x = tid + NT * u;
         const int r = x / RQ, q = x - r * RQ;
         const int I = p0 + r, J = c0 + 4 * q;
         const bool in = x < RP * RQ && I < Np && J < Nt;
@@ -1836,10 +1846,11 @@ __global__ __launch_bounds__(256) void k_owner_lists(const int4 *__restrict__ it
                                                      int32_t *colour_list)
 {
     constexpr int CP = owner_colours_p<TP, TT>(), CT = owner_colours_t<TT>();
+    static_assert(CP * CT <= kMaxColours, "counters of the colour lists");
     const int nitems_all = counters[2];
     const int lane = threadIdx.x & 63;
     const int stride = gridDim.x * blockDim.x;
-    // whole wavefronts iterate together: one atomic per colour per wavefront
+    // whole wavefronts iterate together: one atomic per list per wavefront
     for (int i0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); i0 < nitems_all; i0 += stride) {
         const int itm = i0 + lane;
         int c = -1;
@@ -1849,14 +1860,15 @@ __global__ __launch_bounds__(256) void k_owner_lists(const int4 *__restrict__ it
                 const EventCtx &E = B ? bt.ev[find_event(bt.tile_base, bt.nev, it.x)] : e0;
                 const int local = it.x - E.tile_base;
                 const int tp = local / E.ntt, tt = local - tp * E.ntt;
-                c = (tp % CP) * CT + tt % CT;
+                const int ndepos = tile_off[it.x + 1] - it.y;
+                c = 2 * ((tp % CP) * CT + tt % CT) + (chunks_of(ndepos) <= kLightItems ? 1 : 0);
             }
         }
         int base = 0;
         if (SCATTER)
-            for (int u = 0; u < CP * CT; ++u)
+            for (int u = 0; u < 2 * CP * CT; ++u)
                 base += (u < c) ? counters[kColourCount + u] : 0;
-        for (int u = 0; u < CP * CT; ++u) {
+        for (int u = 0; u < 2 * CP * CT; ++u) {
             const uint64_t m = __ballot(c == u);
             if (!m)
                 continue;
@@ -1886,30 +1898,49 @@ __global__ __launch_bounds__(64 * kOwnerWaves) void k_raster_owner(
     __shared__ double xsum[NW * kBatchItems];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int nitems_all = counters[2];
-    const int colour = colour_p * CT + colour_t;
+    const int list = 2 * (colour_p * CT + colour_t);
     int base = 0;
-    for (int c = 0; c < colour; ++c)
+    for (int c = 0; c < list; ++c)
         base += counters[kColourCount + c];
-    const int ntiles_c = counters[kColourCount + colour];
-    for (int k = blockIdx.x; k < ntiles_c; k += gridDim.x) {
-        const int itm = colour_list[base + k];
-        const int tile = items[itm].x;
-        const EventCtx &E = B ? bt.ev[find_event(bt.tile_base, bt.nev, tile)] : e0;
-        const int local = tile - E.tile_base;
-        const int tp = local / E.ntt, tt = local - tp * E.ntt;
-        float4 *mine = acc4 + w * RQ4;
+    const int nheavy = counters[kColourCount + list], nlight = counters[kColourCount + list + 1];
+    float4 *mine = acc4 + w * RQ4;
+    double *xs = xsum + w * kBatchItems;
+    // draws items first, first + step, ... of the tile that item `itm` opens
+    auto draw = [&](int itm, int tile, int first, int step) {
         for (int x = lane; x < RQ4; x += 64)
             mine[x] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         wave_lds_sync();
-        for (int j = itm + w; j < nitems_all; j += NW) {
+        for (int j = itm + first; j < nitems_all; j += step) {
             const int4 it = items[j];
             if (it.x != tile)
                 break;
-            raster_item<TP, TT, B, FLUCT, true>(mine, xsum + w * kBatchItems, it, records, e0, bt);
+            raster_item<TP, TT, B, FLUCT, true>(mine, xs, it, records, e0, bt);
         }
-        __syncthreads();  // every copy of the region is complete
-        owner_flush<RP, RT, NW, 64 * NW>(acc4, glb(E.grid), E.kp.Np, E.kp.Nt, tp * TP, tt * TT);
-        __syncthreads();  // the copies are read before the next tile clears them
+        wave_lds_sync();
+    };
+    const int nlg = (nlight + NW - 1) / NW;  // light tiles: one per wavefront
+    for (int k = blockIdx.x; k < nheavy + nlg; k += gridDim.x) {
+        const bool heavy = k < nheavy;
+        const int at = heavy ? k : nheavy + (k - nheavy) * NW + w;
+        if (!heavy && at >= nheavy + nlight)
+            continue;
+        const int itm = __builtin_amdgcn_readfirstlane(colour_list[base + at]);
+        const int tile = __builtin_amdgcn_readfirstlane(items[itm].x);
+        const EventCtx &E = B ? bt.ev[find_event(bt.tile_base, bt.nev, tile)] : e0;
+        const int local = tile - E.tile_base;
+        const int tp = local / E.ntt, tt = local - tp * E.ntt;
+        if (heavy) {
+            draw(itm, tile, w, NW);
+            __syncthreads();  // every copy of the region is complete
+            owner_flush<RP, RT, NW, 64 * NW>(acc4, glb(E.grid), E.kp.Np, E.kp.Nt, tp * TP, tt * TT,
+                                             threadIdx.x);
+            __syncthreads();  // the copies are read before the next tile clears them
+        } else {
+            draw(itm, tile, 0, 1);
+            owner_flush<RP, RT, 1, 64>(mine, glb(E.grid), E.kp.Np, E.kp.Nt, tp * TP, tt * TT,
+                                       lane);
+            wave_lds_sync();
+        }
     }
 }
 
