@@ -354,7 +354,9 @@ __device__ __forceinline__ double surviving_charge(const Win &w, const PlanePara
     const uint4 r = philox4x32_10(make_uint4(0u, 0u, (uint32_t)d, event), P.lkey0, P.lkey1);
     const double ua = ((double)(r.x >> 9) + 0.5) * 0x1p-23;
     const double ub = ((double)(r.y >> 9) + 0.5) * 0x1p-23;
-    const double z = sqrt(-2.0 * log(ua)) * cospi(2.0 * ub);
+    double c, sn;
+    cos_sin_turns(ub, c, sn);
+    const double z = sqrt_pos_d(-2.0 * ln_uniform(ua)) * c;
     const double F = w.q * p + z * sqrt(w.q * p * (1.0 - p));
     return (F < 0.0) ? 0.0 : F;
 }
@@ -1185,10 +1187,14 @@ __device__ __forceinline__ double bin_integral(double ca, bool na, double cb, bo
     return (2.0 - ca) - cb;
 }
 
-__device__ __forceinline__ void thread_axis_weights(int lo, int n, double mu, double s, float *W)
+// `part` of `parts`: only the bins n part / parts .. n (part + 1) / parts - 1
+// (the outer edges are evaluated by every part).
+__device__ __forceinline__ void thread_axis_weights(int lo, int n, double mu, double s, float *W,
+                                                    int part = 0, int parts = 1)
 {
     if (s == 0.0) {
-        W[0] = 1.0f;
+        if (part == 0)
+            W[0] = 1.0f;
         return;
     }
     const double inv = 1.0 / (kSqrt2 * s);
@@ -1197,14 +1203,18 @@ __device__ __forceinline__ void thread_axis_weights(int lo, int n, double mu, do
     const double c_n = edge_tail(lo, n, mu, inv, nn);
     const double rtot = 1.0 / bin_integral(c_lo, n0, c_n, nn);
     bool n_lo = n0;
-    for (int i = 0; i + 1 < n; ++i) {
+    const int i0 = n * part / parts, i1 = n * (part + 1) / parts;
+    if (i0 > 0 && i0 < i1)
+        c_lo = edge_tail(lo, i0, mu, inv, n_lo);
+    for (int i = i0; i < min(i1, n - 1); ++i) {
         bool n_hi;
         const double c_hi = edge_tail(lo, i + 1, mu, inv, n_hi);
         W[i] = (float)(bin_integral(c_lo, n_lo, c_hi, n_hi) * rtot);
         c_lo = c_hi;
         n_lo = n_hi;
     }
-    W[n - 1] = (float)(bin_integral(c_lo, n_lo, c_n, nn) * rtot);  // the last edge is c_n
+    if (i1 == n)
+        W[n - 1] = (float)(bin_integral(c_lo, n_lo, c_n, nn) * rtot);  // the last edge is c_n
 }
 
 // Patch values of a patch set (flat, at the scanned offsets).  A wavefront takes
@@ -1396,16 +1406,16 @@ __device__ __forceinline__ void clear_blocks(gptr<float> grid, int Np, int Nt, i
     }
 }
 
-// Two wavefronts per block of 64 depos: lane l of the first computes depo
-// l's header and pitch weights into LDS, lane l of the second its tick
-// weights (two FP64 chains per depo in flight instead of one, for the same
-// LDS), then the block writes the records out one 256-byte row at a time.
-// The first `nclr` blocks instead clear the occupied blocks of the grids, one
-// part of a band of kOccRows rows per wavefront at a time (nbands bands over
-// all events): the clear is bound by HBM writes and the records by FP64
-// arithmetic, so one launch runs both side by side.
-template <bool B>
-__global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables bt, int64_t ntotal,
+// NW wavefronts per block of 64 depos: lane l of the last computes depo l's
+// header, charge and tick weights into LDS, lane l of the others its pitch
+// weights in NW - 1 parts (several FP64 chains per depo in flight for the same
+// LDS), then the block writes the records out one 256-byte row at a time.  The
+// first `nclr` blocks instead clear the occupied blocks of the grids, one part of
+// a band of kOccRows rows per wavefront at a time (nbands bands over all events):
+// the clear is bound by HBM writes and the records by FP64 arithmetic, so one
+// launch runs both side by side.
+template <bool B, int NW>
+__global__ __launch_bounds__(64 * NW) void k_fill_records(EventCtx e0, BatchTables bt, int64_t ntotal,
                                                      const int32_t *depo_tile,
                                                      const int32_t *depo_slot,
                                                      const int32_t *tile_off, float *records,
@@ -1414,7 +1424,7 @@ __global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables b
     __shared__ float stage[64 * kStageStride];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if ((int)blockIdx.x < nclr) {
-        for (int u = 2 * blockIdx.x + wv; u < nbands << parts_shift; u += 2 * nclr) {
+        for (int u = NW * blockIdx.x + wv; u < nbands << parts_shift; u += NW * nclr) {
             const int gb = u >> parts_shift, part = u & ((1 << parts_shift) - 1);
             const int e = B ? find_event(bt.band_base, bt.nev, gb) : 0;
             const EventCtx &E = B ? bt.ev[e] : e0;
@@ -1437,7 +1447,9 @@ __global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables b
         int *h = (int *)rec;
         const int off = w.lo_t & 3;
         const int nq = quad_of(w.lo_t + w.n_t - 1) - quad_of(w.lo_t) + 1;
-        if (wv == 0) {  // header and pitch weights
+        if (wv < NW - 1) {
+            thread_axis_weights(w.lo_p, w.n_p, w.mu_p, w.s_p, rec + kRecWp, wv, NW - 1);
+        } else {
             h[kHLoP] = w.lo_p;
             h[kHLoT] = w.lo_t;
             h[kHNp] = w.n_p;
@@ -1447,8 +1459,6 @@ __global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables b
             h[kHQlo] = (int)(uint32_t)__double_as_longlong(qs);
             h[kHQhi] = (int)(uint32_t)((uint64_t)__double_as_longlong(qs) >> 32);
             h[kHMq] = magic_small(nq);
-            thread_axis_weights(w.lo_p, w.n_p, w.mu_p, w.s_p, rec + kRecWp);
-        } else {  // tick weights
             float *Wt = rec + kRecWt;
             for (int k = 0; k < off; ++k)
                 Wt[k] = 0.0f;
@@ -1458,7 +1468,7 @@ __global__ __launch_bounds__(128) void k_fill_records(EventCtx e0, BatchTables b
         }
     }
     __syncthreads();
-    for (int r = wv; r < 64; r += 2) {
+    for (int r = wv; r < 64; r += NW) {
         const int pr = __builtin_amdgcn_readlane(pos, r);
         if (pr >= 0)
             records[(int64_t)pr * kRecWords + lane] = stage[r * kStageStride + lane];
@@ -2343,6 +2353,14 @@ hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *
 constexpr int kMaxClearBlocks = 4096;
 constexpr int kClearWaves = 512;
 
+// Up to this many depos a record block has four wavefronts instead of two: the
+// pitch edges of a depo in three parts, each a chain of FP64 erfc, where the
+// launch cannot fill the chip anyway (the window and the outer edges are then
+// evaluated by each part).  Record kernel with two / four: 1,000 uniform depos 13.3 /
+// 9.0 us, 20,000 track depos 12.3 / 9.1, 50,000 14.9 / 14.4, 100,000 23.6 / 25.0,
+// 500,000 67 / 77.
+constexpr int64_t kWideRecords = 32768;
+
 static size_t sched_blocks_of(int64_t ntiles)
 {
     return (size_t)((ntiles + 1 + kSchedTiles - 1) / kSchedTiles);
@@ -2582,10 +2600,12 @@ static hipError_t raster_sequence(const wcsim_plane *pl, const EventCtx &e0,
     int parts_shift = 0;
     while (parts_shift < 3 && (nbands << parts_shift) < kClearWaves)
         ++parts_shift;
+    const int nw = n <= kWideRecords ? 4 : 2;
     const int nclr =
-        (int)std::min<int64_t>(kMaxClearBlocks, ((nbands << parts_shift) + 1) / 2);
-    hipLaunchKernelGGL(k_fill_records<B>, dim3(blocks_for(n, 64) + nclr), dim3(128), 0, s, e0, bt,
-                       n, w.depo_tile, w.depo_slot, w.tile_count, w.records, (int)nbands, nclr,
+        (int)std::min<int64_t>(kMaxClearBlocks, ((nbands << parts_shift) + nw - 1) / nw);
+    auto *records = nw == 4 ? k_fill_records<B, 4> : k_fill_records<B, 2>;
+    hipLaunchKernelGGL(records, dim3(blocks_for(n, 64) + nclr), dim3(64 * nw), 0, s, e0, bt, n,
+                       w.depo_tile, w.depo_slot, w.tile_count, w.records, (int)nbands, nclr,
                        parts_shift);
     if ((e = hipGetLastError()) != hipSuccess || (e = mark(0)) != hipSuccess)
         return e;
