@@ -530,8 +530,8 @@ struct FftCt {
 // read from the table, so that the factors of a radix-16 pass are no further off
 // than those of a radix-8 pass by repeated products of w.
 // Measured against radix-2..8 passes with a copy through LDS at both ends: 4800
-// rows of 1600 points forward 122 -> 42 us, inverse 86 -> 42 us (2.8 TB/s of the
-// rows and spectra); 3330 rows of 2187 points forward 79 -> 28 us.
+// rows of 1600 points forward 122 -> 36 us, inverse 86 -> 40 us (3 TB/s of the
+// rows and spectra); 3330 rows of 2187 points forward 79 -> 26 us.
 // ---------------------------------------------------------------------------
 constexpr int gen_per_thread(int R) { return R >= 9 ? 1 : 16 / R; }
 
@@ -642,10 +642,9 @@ __device__ __forceinline__ void gen_pass_any(float2 *row, const float2 *tab, con
 
 struct FftGen {
     static constexpr int kMaxThreads = 1024;
-    // Wavefronts per SIMD that the register allocation aims at: the radix-16
-    // pass would take 98 registers (4 wavefronts); held to 80, passes A and C of
-    // 4800 rows of 1600 points take 5% less time, and at 8 wavefronts (64
-    // registers) longer rows lose more than that again.
+    // Wavefronts per SIMD that the register allocation aims at (80 registers):
+    // left alone, the radix-16 passes took 83 to 98 (4 or 5 wavefronts) and 4800
+    // rows of 1600 points 5% longer; at 8 wavefronts longer rows lost that again.
     static constexpr int kMinWaves = 6;
     GenPlan plan;
     template <class Load, class Store>
@@ -717,8 +716,8 @@ __device__ __forceinline__ void load_tables(const TwTables &t, float2 *la, float
 // Pass A: tick-axis real FFT of rows.  Real rows of length ncols (zero padded
 // to 2 N2) are packed as z_n = x_{2n} + i x_{2n+1}; Z = FFT_N2(z) gives
 // X_k = E_k - i w^k D_k and X_{N2-k} = conj(E_k + i w^k D_k), with
-// E_k = (Z_k + conj Z_{N2-k}) / 2, D_k = (Z_k - conj Z_{N2-k}) / 2 and
-// w = exp(-2 pi i / N').  Output chunk layout X[c][row][f], k = c F + f,
+// E_k = Z_k + conj Z_{N2-k}, D_k = Z_k - conj Z_{N2-k} and w = exp(-2 pi i / N'):
+// twice the spectrum (exactly; the response spectra are halved).  Output chunk layout X[c][row][f], k = c F + f,
 // frequencies above N2 zero.
 // Workgroups of (threads of a row, rows): thread (x, y) works on row y alone.
 // LDS: rows [rows][N2 + 1], then the N2 table, then the N' table.
@@ -734,9 +733,22 @@ struct R2CIo {
     int occ_shift;
 };
 
-// Loads of grid blocks that the occupancy map leaves unmarked read this pair
-// of zeros instead (one cached line for the whole launch).
-__device__ const float2 g_zero_pair[1] = {};
+// Loads of a workgroup's rows through a buffer descriptor: an offset past its
+// end reads as zero without an access, so the zero padding and the grid blocks
+// that the occupancy map leaves unmarked cost one select of the offset.
+// (Clamped addresses and selects of the values: pass A of 9600 x 6000 cells 109
+// us, 106 so; of 4800 x 3000 39 and 36; registers 50 -> 35 and 98 -> 60.)
+constexpr uint32_t kNoLoad = 0x80000000u, kBufferBytes = 0x7ffffffcu;
+constexpr int kBufferFormat = 0x00020000;  // raw 32-bit elements, no swizzle
+
+template <class T>
+__device__ __forceinline__ T *uniform_ptr(T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (T *)((uint64_t)hi << 32 | lo);
+}
 
 template <class FFT, bool BATCH>
 __global__ __launch_bounds__(FFT::kMaxThreads)
@@ -787,49 +799,80 @@ __attribute__((amdgpu_waves_per_eu(FFT::kMinWaves))) void k_rows_r2c(R2CIo io, B
             return;
         }
     }
-    // z_n of row s straight from global memory into the first pass.  Every
-    // load is issued unconditionally from a clamped (valid) address and the
-    // padding is selected afterwards, so the loads of a pass stay in flight
-    // together instead of waiting on each other across branches.  Loads in
-    // unoccupied blocks read the zero pair instead (the two ticks of a load
-    // share a block: blocks are at least 64 ticks and t is even).
-    auto load2 = [&](int s, int n) {  // even ncols and stride: one 8-byte load
-        const int row = row0 + s, t = 2 * n;
-        const int tc = min(t, ncols - 2);
-        const gptr<const float> src = in + (int64_t)min(row, nrows - 1) * in_stride + tc;
-        const bool occ = (occ_m >> (tc >> osh)) & 1ull;
-        const float2 v = *(occ ? (gptr<const float2>)src : glb(g_zero_pair));
-        const bool ok = row < nrows && t < ncols;
-        return ok ? v : make_float2(0.0f, 0.0f);
+    // z_n of row s straight from global memory into the first pass; every load
+    // is issued, so that those of a pass are in flight together.  The two ticks
+    // of z_n share an occupancy block (blocks are at least 64 ticks, t is even).
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)uniform_ptr(io.in + (int64_t)row0 * in_stride), 0, kBufferBytes, kBufferFormat);
+    const int stride = (int)in_stride;
+    const bool row_ok = my_row < nrows;
+    auto load = [&](auto mapped, auto pairs) {
+        return [=](int s, int n) {
+            const int t = 2 * n;
+            bool ok = row_ok && t < ncols;
+            if constexpr (decltype(mapped)::value)
+                ok = ok && ((occ_m >> (t >> osh)) & 1ull);
+            const uint32_t off = 4u * (uint32_t)(s * stride + t);
+            if constexpr (decltype(pairs)::value) {  // even ncols and stride
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rows, ok ? off : kNoLoad, 0, 0);
+                return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+            } else {
+                const uint32_t x = __builtin_amdgcn_raw_buffer_load_b32(rows, ok ? off : kNoLoad, 0, 0);
+                const uint32_t y = __builtin_amdgcn_raw_buffer_load_b32(
+                    rows, (ok && t + 1 < ncols) ? off + 4u : kNoLoad, 0, 0);
+                return make_float2(__uint_as_float(x), __uint_as_float(y));
+            }
+        };
     };
-    auto load1 = [&](int s, int n) {
-        const int row = row0 + s, t = 2 * n;
-        const gptr<const float> src = in + (int64_t)min(row, nrows - 1) * in_stride;
-        const int ta = min(t, ncols - 1), tb = min(t + 1, ncols - 1);
-        const bool occ = (occ_m >> (ta >> osh)) & 1ull;
-        const gptr<const float> zf = (gptr<const float>)glb(g_zero_pair);
-        const float a = *(occ ? src + ta : zf), b = *(occ ? src + tb : zf);
-        const bool ok = row < nrows;
-        return make_float2((ok && t < ncols) ? a : 0.0f, (ok && t + 1 < ncols) ? b : 0.0f);
-    };
-    if ((ncols & 1) == 0 && (in_stride & 1) == 0)
-        fft.run_io(lds, tabN2, load2, InLds{});
-    else
-        fft.run_io(lds, tabN2, load1, InLds{});
+    using yes = std::true_type;
+    using no = std::false_type;
+    if ((ncols & 1) == 0 && (in_stride & 1) == 0) {
+        if (io.occ)
+            fft.run_io(lds, tabN2, load(yes{}, yes{}), InLds{});
+        else
+            fft.run_io(lds, tabN2, load(no{}, yes{}), InLds{});
+    } else {
+        if (io.occ)
+            fft.run_io(lds, tabN2, load(yes{}, no{}), InLds{});
+        else
+            fft.run_io(lds, tabN2, load(no{}, no{}), InLds{});
+    }
     // Unpacking straight to the output: the pair (k, N2 - k) goes from LDS to
     // its two chunk slots, and the padding frequencies above N2 get zeros.
+    // X is twice the spectrum: the response spectra carry the other half.
     if (my_row >= nrows)
         return;
     const int half = N2 / 2;
     const float2 *b = lds + (int)threadIdx.y * S;
-    for (int k = threadIdx.x; k <= half; k += blockDim.x) {
-        const int kn = (k == 0) ? 0 : N2 - k;
-        const float2 Zk = b[k], Zn = b[kn];
-        const float2 E = make_float2(0.5f * (Zk.x + Zn.x), 0.5f * (Zk.y - Zn.y));
-        const float2 D = make_float2(0.5f * (Zk.x - Zn.x), 0.5f * (Zk.y + Zn.y));
+    auto pair = [&](int k, float2 &lo, float2 &hi) {
+        const float2 Zk = b[k], Zn = b[(k == 0) ? 0 : N2 - k];
+        const float2 E = make_float2(Zk.x + Zn.x, Zk.y - Zn.y);
+        const float2 D = make_float2(Zk.x - Zn.x, Zk.y + Zn.y);
         const float2 wD = cmul(tw_at(tabH, k), D);
-        put(k, csub(E, mul_pi(wD)));
-        put((k == 0) ? N2 : kn, conjf2(cadd(E, mul_pi(wD))));
+        lo = csub(E, mul_pi(wD));
+        hi = conjf2(cadd(E, mul_pi(wD)));
+    };
+    if ((blockDim.x & (F - 1)) == 0) {
+        // a thread's next frequency lies whole chunks away: its two places move by
+        // a constant
+        const int64_t step = (int64_t)(blockDim.x >> F_shift) * nrows << F_shift;
+        int k = threadIdx.x;
+        gptr<float2> up = X + ((((int64_t)(k >> F_shift) * nrows + my_row) << F_shift) + (k & (F - 1)));
+        const int m = N2 - k;  // (negative for a thread without a pair)
+        gptr<float2> dn = X + ((((int64_t)(m >> F_shift) * nrows + my_row) << F_shift) + (m & (F - 1)));
+        for (; k <= half; k += blockDim.x, up += step, dn -= step) {
+            float2 lo, hi;
+            pair(k, lo, hi);
+            *up = lo;
+            *dn = hi;
+        }
+    } else {
+        for (int k = threadIdx.x; k <= half; k += blockDim.x) {
+            float2 lo, hi;
+            pair(k, lo, hi);
+            put(k, lo);
+            put(N2 - k, hi);
+        }
     }
     for (int k = N2 + 1 + threadIdx.x; k < CF; k += blockDim.x)
         put(k, make_float2(0.0f, 0.0f));
@@ -1752,7 +1795,8 @@ hipError_t build_response_spectrum(wcsim_plane *pl, const float *resp_dev, void 
     hipError_t e;
     if ((e = rows_r2c(pl, resp_dev, pl->Rp, pl->Rt, pl->Rt, XR, s)) != hipSuccess)
         return e;
-    const float scale = (float)(1.0 / ((double)pl->L * (double)pl->Nfft));
+    // XR is twice the rows' spectrum, and so is the grid's X that the result meets
+    const float scale = (float)(0.25 / ((double)pl->L * (double)pl->Nfft));
     if ((e = pitch_pass(pl, XR, pl->Rp, nullptr, pl->K, pl->L, 1, 2, scale, s)) != hipSuccess)
         return e;
     if (!pl->poly)
@@ -1760,7 +1804,7 @@ hipError_t build_response_spectrum(wcsim_plane *pl, const float *resp_dev, void 
     const int64_t total = (int64_t)pl->C * pl->kp.nimpact * kPolyM * pl->F;
     hipLaunchKernelGGL(k_poly_spectrum, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, XR,
                        pl->Rp, pl->C, pl->F, (int)pl->kp.nimpact, pl->polyA,
-                       1.0 / ((double)kPolyM * (double)pl->Nfft), pl->KP);
+                       0.25 / ((double)kPolyM * (double)pl->Nfft), pl->KP);
     return hipGetLastError();
 }
 
