@@ -8,15 +8,16 @@
 // each one HBM read and one HBM write of its operand:
 //   A  tick-axis real FFT of every pitch row, zero-padded to N' = 2 N2 >=
 //      Nt + Rt - 1 (no wrap-around), written as column chunks [C][Np][F] of
-//      F consecutive frequencies so that the next pass reads whole chunks;
+//      F consecutive frequencies so that the next pass reads whole chunks (X
+//      holds twice the spectrum);
 //   B  per frequency chunk and pitch block: overlap-save along pitch.  A block
 //      of L rows (the V = L - Rp + 1 output rows plus Rp - 1 rows of history)
 //      is transformed in LDS, multiplied by the resident response spectrum
-//      K = DFT_{L x N'}(R) / (L N'), transformed back, and the V valid rows are
-//      kept (all rows, or only each wire's centre impact row);
+//      K = DFT_{L x N'}(R) / (2 L N'), transformed back, and the V valid rows
+//      are kept (all rows, or only each wire's centre impact row);
 //   C  tick-axis inverse real FFT of every kept row, cropped to Nt ticks.
 // No step is a dense contraction, so there is no MFMA: the transforms are
-// mixed-radix (2, 3, 4, 5, 8) self-sorting Stockham passes over LDS, each pass
+// mixed-radix (2 to 16) self-sorting Stockham passes over LDS, each pass
 // staging its butterflies in registers between two barriers so one LDS buffer
 // suffices.  Twiddles come from two small FP64-derived tables per transform
 // size held in LDS (W^j = Hi[j / 64] Lo[j mod 64]), so no pass waits on global
@@ -990,7 +991,7 @@ __attribute__((amdgpu_waves_per_eu(FFT::kMinWaves))) void k_rows_c2r(C2RIo io, B
 // a block are n = n0 + D w (n0 fixed by the block's first row), and
 //   y[n0 + D w] = sum_{k'<L/D} Z[k'] exp(2 pi i k' w / (L/D)),
 //   Z[k'] = exp(2 pi i k' n0 / L) sum_{j<D} P[k' + j L/D] exp(2 pi i j n0 / D),
-// P the block spectrum times the response spectrum (which carries 1/(L N')).
+// P the block spectrum times the response spectrum (which carries 1/(2 L N')).
 // So the inverse runs at length L/D on the folded spectrum instead of L.
 // LDS: the block [L][Fb], the folded block [L/D][Fb] (fold only), then the L
 // table and the L/D table.
@@ -1151,7 +1152,7 @@ __global__ __launch_bounds__(FFT::kMaxThreads) void k_pitch_conv(PitchIo io, Bat
 // D convolutions of wire-rate phase sequences with A-tap filters, summed.
 // Overlap-save along wires with blocks of M = 128: block w0 takes
 // x_b[j] = G_{phi_b}[w0 + s_b - (A - 1) + j] (j < M), forms
-// Y(f) = sum_b H_b(f) DFT_M(x_b)(f) with H_b = DFT_M(h_b) / (M N') resident,
+// Y(f) = sum_b H_b(f) DFT_M(x_b)(f) with H_b = DFT_M(h_b) / (2 M N') resident,
 // and keeps y[j] = IDFT_M(Y)[j], j >= A - 1, as out[w0 + j - (A - 1)].
 // A workgroup takes one block of V = M - A + 1 wires for all F columns of a
 // chunk.  Per phase: a radix-8 pass from global memory into LDS, then a
@@ -1275,7 +1276,7 @@ __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables
 }
 
 // Response spectra of the polyphase pass: H[c][b][f][s] = sum_{a < A, D a + b < Rp}
-// XR[c][D a + b][s] exp(-2 pi i a f / M) / (M N'), from the tick spectra XR of
+// XR[c][D a + b][s] exp(-2 pi i a f / M) / (2 M N'), from the tick spectra XR of
 // the response rows (FP64 sums, once per plane).
 __global__ void k_poly_spectrum(const float2 *XR, int Rp, int C, int F, int D, int A,
                                 double scale, float2 *H)
@@ -1761,7 +1762,7 @@ size_t response_work_bytes(const wcsim_plane *pl)
 }
 
 // Response spectrum K[c][l][f] = sum_{i<Rp} sum_{s<Rt} R[i][s]
-//   exp(-2 pi i (l i / L + k s / N')) / (L N'), k = c F + f.
+//   exp(-2 pi i (l i / L + k s / N')) / (2 L N'), k = c F + f.
 // Response combined with the electronics response along ticks:
 // out[r][t] = sum_s R[r][s] E[t - s], t < Rt0 + Ne - 1 (FP64 sums).  Runs once
 // per plane creation.

@@ -205,10 +205,10 @@ struct wcsim_plane {
     float2 *twHalf;  // two-level table of exp(-2 pi i k / N'), k <= N2
     float2 *twL;     // two-level table of exp(-2 pi i j / L), j < L
     float2 *twF;     // two-level table of exp(-2 pi i j / L10), j < L10 (fold only)
-    float2 *K;       // response spectrum [C][L][F], scaled by 1/(L N')
+    float2 *K;       // response spectrum [C][L][F], scaled by 1/(2 L N')
     // polyphase wire-output pitch pass (poly): response spectra KP[C][D][M][F]
     // of the D phase filters of polyA = ceil(Rp / D) taps, scaled by
-    // 1/(M N'); blocks of polyV = M - polyA + 1 wires; polyCw = D/2 + r0
+    // 1/(2 M N'); blocks of polyV = M - polyA + 1 wires; polyCw = D/2 + r0
     bool poly;
     int polyA, polyV, polyBlocks, polyCw;
     float2 *KP;
@@ -279,7 +279,6 @@ struct RasterWork {
     int32_t *large;       // [n] depos of the large-patch path
     float *records;       // [n][64] depo records in tile-list order
     uint8_t *occ;         // occupancy maps of the grids (bands x kOccCols bytes)
-    int32_t *sort_tot;    // [256] digit totals of the tile-list sort (zero between passes)
 };
 size_t raster_work_bytes(const wcsim_plane *pl, int64_t n);
 RasterWork raster_work_carve(const wcsim_plane *pl, int64_t n, void *base);
