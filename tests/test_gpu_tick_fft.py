@@ -40,3 +40,20 @@ def test_tick_transform_lengths(n2):
         print("N2 %d nt %d kind %d err %.2g" % (n2, nt, kind, err), flush=True)
         assert err <= 1e-5
     P.destroy()
+
+
+@pytest.mark.parametrize("nt", [100, 101, 1000, 6000])
+def test_a_grid_at_any_float(nt):
+    """A grid that starts one float into its storage gives the aligned grid's
+    output bit for bit (the same arithmetic on the same values)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_01841_amd import wcsim
+    P = wcsim.Plane(W.plane(5, nt), W.physics(False), W.response("bipolar"), r0=105)
+    g = torch.Generator(device="cuda").manual_seed(nt)
+    G = torch.rand((50, nt), generator=g, device="cuda")
+    off = torch.zeros(50 * nt + 1, device="cuda")[1:].view(50, nt)
+    off.copy_(G)
+    for kind in (wcsim.OUT_WIRE, wcsim.OUT_PITCH):
+        assert torch.equal(wcsim.convolve(P, G, kind=kind), wcsim.convolve(P, off, kind=kind))
+    P.destroy()
