@@ -21,7 +21,7 @@
 // staging its butterflies in registers between two barriers so one LDS buffer
 // suffices.  Twiddles come from two small FP64-derived tables per transform
 // size held in LDS (W^j = Hi[j / 64] Lo[j mod 64]), so no pass waits on global
-// memory, and every global<->LDS copy issues its loads in batches.
+// memory, and the loads of a pass from global memory are issued together.
 #include <math.h>
 
 #include <algorithm>
@@ -666,31 +666,6 @@ struct FftGen {
             gen_pass_any<false, true>(row, tab, plan, last, none, store);
     }
 };
-
-// Copy loop with the global accesses of kBatch iterations issued together:
-// value i = load(i) for i < total, then store(i, value).  A plain loop would
-// wait for each load before the LDS store of the same iteration and expose the
-// full memory latency once per iteration.
-constexpr int kBatch = 8;
-template <class LoadF, class StoreF>
-__device__ __forceinline__ void batched_copy(int total, LoadF load, StoreF store)
-{
-    for (int i0 = threadIdx.x; i0 < total; i0 += kBatch * blockDim.x) {
-        float2 v[kBatch];
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int i = i0 + b * blockDim.x;
-            if (i < total)
-                v[b] = load(i);
-        }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int i = i0 + b * blockDim.x;
-            if (i < total)
-                store(i, v[b]);
-        }
-    }
-}
 
 // Twiddle tables (global) of a kernel, copied into LDS.
 struct TwTables {
