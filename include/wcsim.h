@@ -123,7 +123,9 @@ typedef struct {
                          * values and its twiddle tables must fit a workgroup's LDS,
                          * so N' <= 20000 (else WCSIM_E_INVALID) */
     int32_t fft_pitch;  /* pitch-axis overlap-save block transform length L > resp_npitch - 1 */
-    int32_t freq_chunk; /* spectrum columns per chunk (8 or 16) */
+    int32_t freq_chunk; /* spectrum columns per chunk (8 or 16); 0: by the transform
+                         * lengths alone, so that planes of one readout and response
+                         * run in one batch launch whatever their wires */
     int32_t tile;       /* raster tile shape id, pitch bins x ticks of a tile: 0 = 32 x 8
                          * (default), 1 = 32 x 32, 2 = 64 x 8; each wavefront's LDS
                          * region adds a 32-bin x 16-tick halo */
@@ -280,7 +282,8 @@ wcsim_status wcsim_simulate_event(const wcsim_plane *plane, const wcsim_depo *de
  * current device must be the plane's.  Same results as wcsim_simulate_event.
  * Errors: WCSIM_E_INVALID when the event needs more workspace than the array
  * holds (wcsim_simulate_workspace_bytes(plane, n, out_kind) >
- * WCSIM_NOALLOC_SCRATCH_BYTES) or for bad arguments, with nothing launched.
+ * WCSIM_NOALLOC_SCRATCH_BYTES; where the library chose chunks of 16 spectrum
+ * columns, counted with chunks of 8) or for bad arguments, with nothing launched.
  * Every call on one GPU uses that GPU's one array, which keeps the last
  * call's contents (each call clears what it needs): calls whose executions
  * overlap on one GPU (other streams, other threads) race and must not be

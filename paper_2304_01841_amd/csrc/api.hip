@@ -201,7 +201,7 @@ void free_plane(wcsim_plane *p)
 
 constexpr size_t kLdsBytes = 160 * 1024;
 
-wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc)
+wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wcsim_plane *donor)
 {
     const int nmin = (int)(pl->Nt + pl->Rt - 1);
     int nfft = (sc && sc->fft_ticks) ? sc->fft_ticks : smallest_smooth_even(nmin);
@@ -219,16 +219,21 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc)
     // history is Rp - 1 of the L rows).
     int L = (sc && sc->fft_pitch) ? sc->fft_pitch
                                   : std::min(2048, std::max(256, pow2_at_least(4 * pl->Rp)));
-    // Default chunk with long pitch blocks: 16 columns when the tick spectrum of
-    // the grid exceeds 64 MiB, else 8.  Sixteen make whole 128-byte lines of each
-    // pitch row (with 8 the two halves of a line are written and read by
-    // workgroups of different L2s, which costs once the spectrum goes out to
-    // HBM); eight give the pitch passes twice the workgroups.  Wire output, 8 / 16
-    // columns: 960 wires x 6000 ticks 231 / 196 us, 480 x 6000 (115 MiB) 127 / 109,
-    // 300 x 6000 (72 MiB) 71 / 67, 480 x 3000 (59 MiB) 77 / 78, 100 x 6000 (24 MiB)
-    // 41.3 / 41.4, 300 x 1000 28.6 / 32.4.
-    const bool long_lines = sizeof(float2) * (size_t)pl->Np * (pl->N2 + 1) > ((size_t)64 << 20);
-    pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && !long_lines ? 8 : 16);
+    // Default chunk with long pitch blocks: 16 columns for tick transforms of 4096
+    // points or more, else 8.  Sixteen make whole 128-byte lines of each pitch row
+    // (with 8 the two halves of a line are written and read by workgroups of
+    // different L2s, which costs once the spectrum goes out to HBM); eight give the
+    // pitch passes twice the workgroups.  The rule looks at the length alone: planes
+    // that differ in their wires only have to share batch launches and response
+    // spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 230 / 194 us, 300 x
+    // 6000 72 / 67, 24 x 6000 32 / 34, 960 x 4500 175 / 152, 24 x 4500 33 / 33; below
+    // the line 960 x 3000 128 / 112, 480 x 3000 66 / 65, 100 x 3000 36 / 36, 24 x 3000
+    // 28 / 31, 100 x 1000 24 / 27.  Pitch output 960 x 6000 407 / 374, 480 x 3000 114 /
+    // 113.  A batch of 16 events on 100-960 wires x 6000 ticks: 8 columns 2380 us, 16
+    // 1910, 8 for its 100-wire planes and 16 for the others (two classes) 1990.
+    pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && pl->N2 < 2048 ? 8 : 16);
+    pl->wide_by_choice =
+        donor ? donor->wide_by_choice : !(sc && sc->freq_chunk) && L >= 1024 && pl->F == 16;
     if (pl->F != 8 && pl->F != 16)
         return fail(WCSIM_E_INVALID, "freq_chunk must be 8 or 16");
     if (L < pl->Rp)
@@ -356,7 +361,7 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     k.pad_ = 0;
     k.tau = phys->lifetime;
     k.accel = phys->drift_accel;
-    if ((st = choose_schedule(pl, sched)) != WCSIM_OK) {
+    if ((st = choose_schedule(pl, sched, donor)) != WCSIM_OK) {
         free_plane(pl);
         return st;
     }
@@ -909,7 +914,12 @@ wcsim_status wcsim_simulate_event_profiled(const wcsim_plane *pl, const wcsim_de
 // code `scratch` only names the symbol; its device address on each GPU comes
 // from hipGetSymbolAddress, taken once per device and cached.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[WCSIM_NOALLOC_SCRATCH_BYTES];
+// The array is longer than the limit by what a plane of chosen 16-column chunks may
+// need beyond it (wcsim_plane::wide_by_choice): at most 8 columns of both spectra.
+// Such a plane has L >= 1024 and spectra of 2048 columns or more (the rule of
+// choose_schedule), of which 8 are below 1 / 256 of the limit, 256 KiB.
+constexpr size_t kScratchSlack = 512u << 10;
+static __device__ __align__(256) unsigned char scratch[WCSIM_NOALLOC_SCRATCH_BYTES + kScratchSlack];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -946,8 +956,12 @@ wcsim_status wcsim_simulate_event_noalloc(const wcsim_plane *pl, const wcsim_dep
         return fail(WCSIM_E_INVALID, "bad simulate arguments");
     if (out_kind != WCSIM_OUT_WIRE && out_kind != WCSIM_OUT_PITCH)
         return fail(WCSIM_E_INVALID, "bad output kind");
-    const size_t need = wcsim_simulate_workspace_bytes(pl, n, out_kind);
-    if (need > (size_t)WCSIM_NOALLOC_SCRATCH_BYTES)
+    const size_t bytes = wcsim_simulate_workspace_bytes(pl, n, out_kind);
+    const size_t need = pl->wide_by_choice ? bytes - conv_work_bytes(pl, out_kind) +
+                                                 conv_work_bytes_cols(pl, out_kind, 8)
+                                           : bytes;
+    if (need > (size_t)WCSIM_NOALLOC_SCRATCH_BYTES ||
+        bytes > (size_t)WCSIM_NOALLOC_SCRATCH_BYTES + kScratchSlack)
         return fail(WCSIM_E_INVALID,
                     "event needs " + std::to_string(need) +
                         " bytes of workspace; the allocation-free entry point holds " +

@@ -1697,11 +1697,17 @@ hipError_t launch_convolve_batch_c(const wcsim_plane *pl, const BatchTables &bt,
     return rows_c2r_any<true>(pl, C2RIo{}, bt, (unsigned)nblk_c, s);
 }
 
-size_t conv_work_bytes(const wcsim_plane *pl, wcsim_out out_kind)
+size_t conv_work_bytes_cols(const wcsim_plane *pl, wcsim_out out_kind, int F)
 {
     const int64_t nout = (out_kind == WCSIM_OUT_WIRE) ? pl->Nw : pl->Np;
-    return align_up(sizeof(float2) * (size_t)pl->C * pl->F * (size_t)pl->Np) +
-           align_up(sizeof(float2) * (size_t)pl->C * pl->F * (size_t)nout);
+    const size_t cols = (size_t)((pl->H + F - 1) / F) * (size_t)F;
+    return align_up(sizeof(float2) * cols * (size_t)pl->Np) +
+           align_up(sizeof(float2) * cols * (size_t)nout);
+}
+
+size_t conv_work_bytes(const wcsim_plane *pl, wcsim_out out_kind)
+{
+    return conv_work_bytes_cols(pl, out_kind, pl->F);
 }
 
 hipError_t launch_convolve(const wcsim_plane *pl, const float *grid, float *out,

@@ -191,6 +191,10 @@ struct wcsim_plane {
     // FFT schedule: tick axis N' = 2 N2 (real), pitch axis overlap-save blocks
     // of length L with V = L - Rp + 1 valid rows each.
     int Nfft, N2, H, F, C, L, V, nblocks;
+    // F = 16 is the library's choice (or the donor's) where it would have been 8:
+    // the limit of the allocation-free entry point then counts 8-column chunks,
+    // so that the choice refuses no event
+    bool wide_by_choice;
     // Fb: columns per pitch-pass workgroup (divides F); fold: wire output
     // folds the inverse to length L10 = L / nimpact (nimpact divides L)
     int Fb, L10;
@@ -307,6 +311,8 @@ hipError_t launch_clear_unoccupied(float *grid, int Np, int Nt, const uint8_t *o
 
 // FFT convolution passes
 size_t conv_work_bytes(const wcsim_plane *pl, wcsim_out out_kind);
+// the same for chunks of F columns
+size_t conv_work_bytes_cols(const wcsim_plane *pl, wcsim_out out_kind, int F);
 // `ev` (nullable): 3 events recorded after passes A, B and C.  `occ`
 // (nullable): the grid's occupancy map; blocks it does not mark are read as
 // zero.
