@@ -367,7 +367,10 @@ wcsim_status wcsim_simulate_batch(const wcsim_plane *const *planes,
  * launch sequence on `stream`, its three FFT passes as another on a second
  * stream of the library's, so that one chunk's rasterization overlaps the
  * previous chunk's passes; chunk data alternate between two halves of the
- * workspace.  0 for bad arguments. */
+ * workspace.  An event's output is that of wcsim_simulate_event up to float32
+ * rounding (launch shapes, and with them orders of addition, follow the whole
+ * chunk); with deterministic planes it is the same bit for bit.  0 for bad
+ * arguments. */
 int32_t wcsim_batch_chunk_count(const wcsim_plane *const *planes, const int64_t *n,
                                 int32_t nevents, wcsim_out out_kind);
 

@@ -225,10 +225,10 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
     // different L2s, which costs once the spectrum goes out to HBM); eight give the
     // pitch passes twice the workgroups.  The rule looks at the length alone: planes
     // that differ in their wires only have to share batch launches and response
-    // spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 230 / 194 us, 300 x
-    // 6000 72 / 67, 24 x 6000 32 / 34, 960 x 4500 175 / 152, 24 x 4500 33 / 33; below
-    // the line 960 x 3000 128 / 112, 480 x 3000 66 / 65, 100 x 3000 36 / 36, 24 x 3000
-    // 28 / 31, 100 x 1000 24 / 27.  Pitch output 960 x 6000 407 / 374, 480 x 3000 114 /
+    // spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 233 / 197 us, 300 x
+    // 6000 72 / 67, 24 x 6000 33 / 32, 960 x 4500 179 / 153, 24 x 4500 33 / 31; below
+    // the line 960 x 3000 123 / 113, 480 x 3000 66 / 66, 100 x 3000 34 / 37, 24 x 3000
+    // 28 / 32, 100 x 1000 22 / 25.  Pitch output 960 x 6000 407 / 374, 480 x 3000 114 /
     // 113.  A batch of 16 events on 100-960 wires x 6000 ticks: 8 columns 2380 us, 16
     // 1910, 8 for its 100-wire planes and 16 for the others (two classes) 1990.
     pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && pl->N2 < 2048 ? 8 : 16);

@@ -1650,19 +1650,23 @@ void launch_poly(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt,
 }
 
 // The polyphase pitch pass of one plane (io set) or of a batch (tables).  The
-// phases are cut over five groups while the launch has at most one wavefront per
-// CU without, over two while it then has at most 16 per CU (what 124 registers
-// leave room for).  Convolution, wire output, with one group / so: 100 wires x 1000
-// ticks 34.3 / 22.0 us, 200 x 2000 (1.1 wavefronts a CU) 50.3 / 41.7 (five groups
-// 45.4), 200 x 6000 (3.1) 61.5 / 53.6 (five 73.1), 480 x 6000 (7.8) 116.8 / 109.4,
-// 800 x 6000 (12.5: one group).  A plane of reproducible sums keeps one group, so
-// that its sums do not depend on what shares the launch.
+// phases are cut over five groups while the launch has at most one workgroup per
+// CU (a CU then holds nothing else, and five groups of 16 columns fill 82 KB of its
+// LDS), over two while it has at most six per CU with 8 columns or four with 16
+// (two groups take 142 or 144 registers: twelve wavefronts per CU, six such
+// workgroups or three).  Convolution, wire output, one / two / five groups, with the
+// workgroups of the launch on 256 CUs: 8 columns 240 workgroups 47.9 / 38.8 / 35.2
+// us, 288 51.4 / 41.7 / 44.9, 1248 81.1 / 78.2 / 100, 1520 80.4 / 80.4 / 107, 1568
+// 88.1 / 96.3 / 121; 16 columns 216 55.2 / 43.2 / 40.7, 288 58.4 / 48.2 / 56.7, 760
+// 80.3 / 72.6 / 88.5, 1000 114 / 112 / 128, 1368 153 / 158 / 184.  A plane of
+// reproducible sums keeps one group, so that its sums do not depend on what shares
+// the launch; other planes' sums are rounded in the order of the groups.
 template <bool B>
 hipError_t poly_any(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt,
                     unsigned blocks, hipStream_t s)
 {
-    const unsigned waves = blocks * (unsigned)pl->F / 8, cus = 256;
-    const int S = (pl->det || 2 * waves > 16 * cus) ? 1 : (waves > cus) ? 2 : 5;
+    const unsigned cus = (unsigned)device_cus();
+    const int S = (pl->det || blocks > (pl->F == 16 ? 4 : 6) * cus) ? 1 : (blocks > cus) ? 2 : 5;
     if (pl->F == 16)
         S == 1   ? launch_poly<16, 1, B>(pl, io, bt, blocks, s)
         : S == 2 ? launch_poly<16, 2, B>(pl, io, bt, blocks, s)

@@ -2493,7 +2493,7 @@ RasterWork raster_work_carve(const wcsim_plane *pl, int64_t n, void *base)
 }
 
 // Compute units of the current device (cached per device).
-static int device_cus()
+int device_cus()
 {
     static std::atomic<int> cus[64];
     int dev = 0;

@@ -244,6 +244,7 @@ namespace wcs {
 // ---------------------------------------------------------------------------
 // Launch helpers (defined in raster.hip / fft.hip)
 // ---------------------------------------------------------------------------
+int device_cus();  // compute units of the current device (256 if that fails)
 hipError_t launch_fill_zero(void *ptr, size_t bytes, hipStream_t s);
 
 hipError_t launch_combine_response(const float *R, int Rp, int Rt0, const float *E, int Ne,

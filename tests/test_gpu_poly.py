@@ -37,3 +37,24 @@ def test_phases_over_groups(nimpact, wires, ticks):
                   flush=True)
             assert err <= 1e-5 and np.array_equal(got, again)
             P.destroy()
+
+
+@pytest.mark.parametrize("wires,ticks,nimpact", [(700, 1400, 3), (430, 2600, 5)])
+def test_two_groups_of_sixteen_columns(wires, ticks, nimpact):
+    """More than one workgroup per CU and at most four: two groups, 16 columns."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_01841_amd import wcsim
+    rng = np.random.default_rng(wires)
+    Rp = 21 * nimpact - 1
+    R = W.random_response(rng, Rp, 30)
+    P = wcsim.Plane(W.plane(wires, ticks, nimpact=nimpact), W.physics(False), R, r0=Rp // 2,
+                    schedule={"freq_chunk": 16, "wire_mode": 1})
+    wgs = 8 * -(-P.info["nchunks"] // 8) * P.info["wire_blocks"]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert cus < wgs <= 4 * cus
+    G = rng.standard_normal((wires * nimpact, ticks)).astype(np.float32)
+    ref = O.wire_rows(O.convolve(G, R.astype(np.float64), Rp // 2, workers=8), nimpact)
+    got = wcsim.convolve(P, torch.from_numpy(G).cuda()).cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    P.destroy()
