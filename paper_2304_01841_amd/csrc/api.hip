@@ -649,13 +649,13 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
         return r;
     };
     hipError_t e;
-    // one buffer: windows | offsets | scan scratch | list of large patches |
-    // device copy of host depos
+    // one buffer: windows | offsets, number of large patches | scan scratch | list of
+    // large patches | device copy of host depos
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     const size_t off_offs = align_up(sizeof(int32_t) * 4 * nn);
-    const size_t off_scan = off_offs + align_up(sizeof(int64_t) * (nn + 1));
+    const size_t off_scan = off_offs + align_up(sizeof(int64_t) * (nn + 2));
     const size_t off_list = off_scan + align_up(scan_scratch_bytes(n + 1));
-    const size_t off_depos = off_list + align_up(sizeof(int32_t) * (nn + 1));
+    const size_t off_depos = off_list + align_up(sizeof(int32_t) * nn);
     const size_t bytes = off_depos + (mem == WCSIM_MEM_HOST ? sizeof(wcsim_depo) * nn : 0);
     if ((e = P->buffers->take(0, bytes, &P->buf[0])) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch set)"));
@@ -672,20 +672,21 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
             return bail(check_hip(e, "hipMemcpyAsync(depos)"));
         dd = staged;
     }
-    if ((e = launch_patch_sizes(pl, dd, n, P->meta, P->offsets, s)) != hipSuccess ||
+    if ((e = launch_patch_sizes(pl, dd, n, P->meta, P->offsets, list, s)) != hipSuccess ||
         (e = launch_exclusive_scan_i64(P->offsets, n + 1, scratch, s)) != hipSuccess)
         return bail(check_hip(e, "patch sizes"));
-    int64_t total = 0;
-    if ((e = hipMemcpyAsync(&total, P->offsets + n, sizeof(int64_t), hipMemcpyDeviceToHost, s)) !=
+    int64_t sums[2] = {0, 0};  // patch values, large patches
+    if ((e = hipMemcpyAsync(sums, P->offsets + n, sizeof sums, hipMemcpyDeviceToHost, s)) !=
             hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "patch total"));
-    P->nvalues = total;
-    if ((e = P->buffers->take(1, sizeof(float) * (size_t)std::max<int64_t>(total, 1),
+    P->nvalues = sums[0];
+    if ((e = P->buffers->take(1, sizeof(float) * (size_t)std::max<int64_t>(P->nvalues, 1),
                               &P->buf[1])) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch values)"));
     P->values = (float *)P->buf[1].ptr;
-    if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values, list, s)) != hipSuccess)
+    if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values, list,
+                                 (const int32_t *)(P->offsets + n + 1), sums[1], s)) != hipSuccess)
         return bail(check_hip(e, "patch values"));
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "hipStreamSynchronize"));

@@ -507,21 +507,49 @@ hipError_t exclusive_scan(T *data, int64_t n, void *scratch, hipStream_t s)
 // ---------------------------------------------------------------------------
 // Unfused path: patch sizes, flat patch values, flat scatter
 // ---------------------------------------------------------------------------
-__global__ void k_patch_sizes(const wcsim_depo *depos, int64_t n, PlaneParams P, int32_t *meta,
-                              int64_t *sizes)
+// Patches with more than 64 window edges or kWaveItems passes of (row, tick quad)
+// items are beyond k_patch_wave's wavefront; `large` lists them for k_patch_generic
+// and *nlarge counts them, so that the host, which waits for the patch total anyway,
+// can size that launch.
+constexpr int kWaveItems = 3;
+
+__device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (1ull << lane) - 1ull; }
+
+__device__ __forceinline__ bool beyond_wave(const Win &w)
+{
+    const int nq = quad_of(w.lo_t + w.n_t - 1) - quad_of(w.lo_t) + 1;
+    return w.status == 0 && (w.n_p + w.n_t + 2 > 64 || w.n_p * nq > 64 * kWaveItems);
+}
+
+__global__ __launch_bounds__(256) void k_patch_sizes(const wcsim_depo *depos, int64_t n,
+                                                     PlaneParams P, int32_t *meta, int64_t *sizes,
+                                                     int32_t *large, int32_t *nlarge)
 {
     const int64_t d = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
     if (d == 0)
         sizes[n] = 0;
-    if (d >= n)
-        return;
-    const Win w = depo_window(depos[d], P);
-    const bool ok = (w.status == 0);
-    meta[4 * d + 0] = ok ? w.lo_p : 0;
-    meta[4 * d + 1] = ok ? w.lo_t : 0;
-    meta[4 * d + 2] = ok ? w.n_p : 0;
-    meta[4 * d + 3] = ok ? w.n_t : 0;
-    sizes[d] = ok ? (int64_t)w.n_p * w.n_t : 0;
+    Win w{};
+    w.status = 2;
+    if (d < n) {
+        w = depo_window(depos[d], P);
+        const bool ok = (w.status == 0);
+        meta[4 * d + 0] = ok ? w.lo_p : 0;
+        meta[4 * d + 1] = ok ? w.lo_t : 0;
+        meta[4 * d + 2] = ok ? w.n_p : 0;
+        meta[4 * d + 3] = ok ? w.n_t : 0;
+        sizes[d] = ok ? (int64_t)w.n_p * w.n_t : 0;
+    }
+    const bool big = beyond_wave(w);
+    const uint64_t m = __ballot(big);
+    if (m) {
+        int base = 0;
+        if (lane == 0)
+            base = atomicAdd(nlarge, __popcll(m));
+        base = __builtin_amdgcn_readlane(base, 0);
+        if (big)
+            large[base + __popcll(m & lanemask_lt(lane))] = (int32_t)d;
+    }
 }
 
 template <int NT>
@@ -784,8 +812,6 @@ __device__ __forceinline__ bool fits_tile(const Win &w, int p0, int t0, const Ti
         return false;
     return min(w.lo_p + w.n_p, P.Np) <= p0 + g.rp && min(w.lo_t + w.n_t, P.Nt) <= t0 + g.rt;
 }
-
-__device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (1ull << lane) - 1ull; }
 
 // Mark the occupancy-map blocks that a window (status 0: it meets the grid)
 // reaches.  Every writer stores the same value, so no atomics are needed.
@@ -1269,32 +1295,37 @@ __device__ __forceinline__ void thread_axis_weights(int lo, int n, double mu, do
 }
 
 // Patch values of a patch set (flat, at the scanned offsets).  A wavefront takes
-// kWavePatches consecutive depos: lane k forms the window and charge of depo k,
+// `per` consecutive depos: lane k forms the window and charge of depo k,
 // then the patches are drawn one after another.  Every lane evaluates one window
 // edge (the pitch edges first, then the tick edges: erfc tails as in
 // thread_axis_weights), the weights go through LDS, and the (row, tick quad)
 // items of the patch are held in registers until its total is known.  Patches
-// with more edges or items than that, a few of a long drift, are listed for
+// with more edges or items than that (beyond_wave) are left to
 // k_patch_generic.  One workgroup per depo with its barriers, 16 KB of LDS and
 // library erf took 283 us for 100,000 track depos, this 92 us (16 depos a
 // wavefront 106 us, too few wavefronts; held to 80 registers 143 us).
-constexpr int kWavePatches = 8, kWaveItems = 3;
+// A patch is a chain of about 2 us, so a wavefront takes several only once the set
+// has kWaveFill wavefronts of half as many (window and charge are then formed side by
+// side).  Whole rasterize call with one / two / four / eight: 1,000 uniform depos 54 / 56
+// / 59 / 65 us, 8,000 64 / 62 / 62 / 67, 16,000 75 / 71 / 69 / 72, 100,000 185 / 154 /
+// 141 / 139.
+constexpr int kWavePatches = 8;
+constexpr int64_t kWaveFill = 4096;
 constexpr int kWaveWt = 64, kWaveWords = kWaveWt + 72;  // pitch weights, quad-aligned tick weights
 
 template <bool FLUCT>
 __global__ __launch_bounds__(256) void k_patch_wave(const wcsim_depo *__restrict__ depos, int64_t n,
-                                                    PlaneParams P, uint32_t event,
+                                                    PlaneParams P, uint32_t event, int per,
                                                     const int64_t *__restrict__ offsets,
-                                                    float *__restrict__ values, int32_t *list,
-                                                    int32_t *list_count)
+                                                    float *__restrict__ values)
 {
     __shared__ float4 weights[4][kWaveWords / 4];
     const int lane = threadIdx.x & 63;
     float *wl = (float *)weights[threadIdx.x >> 6];
-    const int64_t d0 = (blockIdx.x * 4LL + (threadIdx.x >> 6)) * kWavePatches;
+    const int64_t d0 = (blockIdx.x * 4LL + (threadIdx.x >> 6)) * per;
     if (d0 >= n)
         return;
-    const int K = (int)min((int64_t)kWavePatches, n - d0);
+    const int K = (int)min((int64_t)per, n - d0);
     Win w{};
     w.status = 2;
     double qs = 0.0;
@@ -1309,18 +1340,7 @@ __global__ __launch_bounds__(256) void k_patch_wave(const wcsim_depo *__restrict
     // edge scale 1 / (sqrt(2) s), 0 for a zero width (one bin of weight 1)
     const double inv_p = (w.s_p > 0.0) ? 1.0 / (kSqrt2 * w.s_p) : 0.0;
     const double inv_t = (w.s_t > 0.0) ? 1.0 / (kSqrt2 * w.s_t) : 0.0;
-    const int nq_l = quad_of(w.lo_t + w.n_t - 1) - quad_of(w.lo_t) + 1;
-    const bool big = w.status == 0 && (w.n_p + w.n_t + 2 > 64 || w.n_p * nq_l > 64 * kWaveItems);
-    const uint64_t bigm = __ballot(big);
-    if (bigm) {
-        int base = 0;
-        if (lane == 0)
-            base = atomicAdd(list_count, __popcll(bigm));
-        base = __builtin_amdgcn_readlane(base, 0);
-        if (big)
-            list[base + __popcll(bigm & lanemask_lt(lane))] = (int32_t)(d0 + lane);
-    }
-    uint64_t todo = __ballot(w.status == 0 && !big);
+    uint64_t todo = __ballot(w.status == 0 && !beyond_wave(w));
     while (todo) {
         const int k = __ffsll((unsigned long long)todo) - 1;
         todo &= todo - 1;
@@ -2356,29 +2376,46 @@ hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hi
 }
 
 hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
-                              int32_t *meta, int64_t *sizes, hipStream_t s)
+                              int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s)
 {
+    int32_t *nlarge = (int32_t *)(sizes + n + 1);
+    hipLaunchKernelGGL(k_fill_zero1, dim3(1), dim3(16), 0, s, (unsigned char *)nlarge,
+                       sizeof(int64_t));
     hipLaunchKernelGGL(k_patch_sizes, dim3(blocks_for(std::max<int64_t>(n, 1), 256)), dim3(256), 0,
-                       s, depos, n, pl->kp, meta, sizes);
+                       s, depos, n, pl->kp, meta, sizes, large, nlarge);
     return hipGetLastError();
 }
 
+// The patches beyond a wavefront get a workgroup each: of four wavefronts while they are
+// few, of one when they fill the chip with those (at long drift, at nsigma = 5 or
+// with twice the diffusion most of a set is among them).  Whole call, one wavefront /
+// four: 300 windows of 13,000 bins 209 / 103 us, 789 of 1,500 bins 81 / 74, 3,159 103
+// / 104, 79,920 1026 / 1235 (on 256 workgroups of four for any number: 2684).
+constexpr int64_t kFewLarge = 1024;
+
 hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                                uint64_t event_id, const int64_t *offsets, float *values,
-                               int32_t *list, hipStream_t s)
+                               const int32_t *large, const int32_t *nlarge, int64_t count,
+                               hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    // list[0] counts the patches left to the generic kernel, list + 1 holds them
-    hipLaunchKernelGGL(k_fill_zero1, dim3(1), dim3(16), 0, s, (unsigned char *)list,
-                       sizeof(int32_t));
-    auto *kernel = pl->kp.fluct ? k_patch_wave<true> : k_patch_wave<false>;
-    hipLaunchKernelGGL(kernel, dim3(blocks_for(n, 4 * kWavePatches)), dim3(256), 0, s, depos, n,
-                       pl->kp, (uint32_t)event_id, offsets, values, list + 1, list);
-    const EventCtx e0 = single_event(pl, depos, n, event_id, nullptr);
-    hipLaunchKernelGGL((k_patch_generic<256, true, false>),
-                       dim3((unsigned)std::min<int64_t>(n, 256)), dim3(256), 0, s, e0,
-                       BatchTables{}, list + 1, list, (int64_t)0, offsets, values);
+    if (count < n) {
+        int per = 1;
+        while (per < kWavePatches && n >= 2 * per * kWaveFill)
+            per *= 2;
+        auto *kernel = pl->kp.fluct ? k_patch_wave<true> : k_patch_wave<false>;
+        hipLaunchKernelGGL(kernel, dim3(blocks_for(n, 4 * per)), dim3(256), 0, s, depos, n, pl->kp,
+                           (uint32_t)event_id, per, offsets, values);
+    }
+    if (count > 0) {
+        const EventCtx e0 = single_event(pl, depos, n, event_id, nullptr);
+        const bool few = count <= kFewLarge;
+        auto *kernel = few ? k_patch_generic<256, true, false> : k_patch_generic<64, true, false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(count, 1 << 20)),
+                           dim3(few ? 256 : 64), 0, s, e0, BatchTables{}, large, nlarge,
+                           (int64_t)0, offsets, values);
+    }
     return hipGetLastError();
 }
 

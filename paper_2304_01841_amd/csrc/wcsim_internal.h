@@ -232,7 +232,7 @@ struct wcsim_patches {
     int64_t n;
     int64_t nvalues;
     int32_t *meta;     // [n][4], in buf[0]
-    int64_t *offsets;  // [n+1], in buf[0]
+    int64_t *offsets;  // [n+1] and the number of large patches, in buf[0]
     float *values;     // buf[1]
     int device;
     wcs_patch_buffers::Buffer buf[2];
@@ -260,15 +260,18 @@ hipError_t launch_philox(const uint32_t *ctr, const uint32_t *key, int64_t n, ui
                          hipStream_t s);
 
 // unfused rasterize: per-depo sizes, scan, values
+// `sizes` holds n + 2 words: the last one receives the number of patches listed in
+// `large` (n words), those that launch_patch_values draws by a workgroup each.
 hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
-                              int32_t *meta, int64_t *sizes, hipStream_t s);
+                              int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s);
 size_t scan_scratch_bytes(int64_t n);
 hipError_t launch_exclusive_scan_i64(int64_t *data, int64_t n, void *scratch, hipStream_t s);
 hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hipStream_t s);
-// `list`: n + 1 words of scratch (the patches too large for a wavefront)
+// `count`: *nlarge, as the host has read it
 hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                                uint64_t event_id, const int64_t *offsets, float *values,
-                               int32_t *list, hipStream_t s);
+                               const int32_t *large, const int32_t *nlarge, int64_t count,
+                               hipStream_t s);
 hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *meta,
                                const int64_t *offsets, const float *values, float *grid,
                                hipStream_t s);
