@@ -649,8 +649,8 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
         return r;
     };
     hipError_t e;
-    // one buffer: windows | offsets, number of large patches | scan scratch | list of
-    // large patches | device copy of host depos
+    // one buffer: windows | offsets, PatchSums | scan scratch | list of large patches |
+    // device copy of host depos
     const size_t nn = (size_t)std::max<int64_t>(n, 1);
     const size_t off_offs = align_up(sizeof(int32_t) * 4 * nn);
     const size_t off_scan = off_offs + align_up(sizeof(int64_t) * (nn + 2));
@@ -675,18 +675,23 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
     if ((e = launch_patch_sizes(pl, dd, n, P->meta, P->offsets, list, s)) != hipSuccess ||
         (e = launch_exclusive_scan_i64(P->offsets, n + 1, scratch, s)) != hipSuccess)
         return bail(check_hip(e, "patch sizes"));
-    int64_t sums[2] = {0, 0};  // patch values, large patches
-    if ((e = hipMemcpyAsync(sums, P->offsets + n, sizeof sums, hipMemcpyDeviceToHost, s)) !=
+    struct {
+        int64_t total;
+        PatchSums more;
+    } sums{};
+    if ((e = hipMemcpyAsync(&sums, P->offsets + n, sizeof sums, hipMemcpyDeviceToHost, s)) !=
             hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "patch total"));
-    P->nvalues = sums[0];
+    P->nvalues = sums.total;
+    P->close = sums.more.close >= 0;
     if ((e = P->buffers->take(1, sizeof(float) * (size_t)std::max<int64_t>(P->nvalues, 1),
                               &P->buf[1])) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch values)"));
     P->values = (float *)P->buf[1].ptr;
     if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values, list,
-                                 (const int32_t *)(P->offsets + n + 1), sums[1], s)) != hipSuccess)
+                                 &((const PatchSums *)(P->offsets + n + 1))->nlarge,
+                                 sums.more.nlarge, s)) != hipSuccess)
         return bail(check_hip(e, "patch values"));
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
         return bail(check_hip(e, "hipStreamSynchronize"));
@@ -754,7 +759,7 @@ wcsim_status wcsim_scatter_add(const wcsim_plane *pl, const wcsim_patches *P, fl
     hipStream_t s = (hipStream_t)stream;
     if (zero_first)
         WCS_HIP(launch_fill_zero(grid, sizeof(float) * (size_t)pl->Np * pl->Nt, s));
-    WCS_HIP(launch_scatter_flat(pl, P->n, P->meta, P->offsets, P->values, grid, s));
+    WCS_HIP(launch_scatter_flat(pl, P->n, P->close, P->meta, P->offsets, P->values, grid, s));
     return WCSIM_OK;
 }
 

@@ -521,9 +521,13 @@ __device__ __forceinline__ bool beyond_wave(const Win &w)
     return w.status == 0 && (w.n_p + w.n_t + 2 > 64 || w.n_p * nq > 64 * kWaveItems);
 }
 
+// Cells of a wavefront's LDS region in k_scatter_flat, and the neighbours that
+// PatchSums::close looks at together.
+constexpr int kScatCells = 1536, kCloseDepos = 8;
+
 __global__ __launch_bounds__(256) void k_patch_sizes(const wcsim_depo *depos, int64_t n,
                                                      PlaneParams P, int32_t *meta, int64_t *sizes,
-                                                     int32_t *large, int32_t *nlarge)
+                                                     int32_t *large, PatchSums *sums)
 {
     const int64_t d = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63;
@@ -531,9 +535,10 @@ __global__ __launch_bounds__(256) void k_patch_sizes(const wcsim_depo *depos, in
         sizes[n] = 0;
     Win w{};
     w.status = 2;
+    bool ok = false;
     if (d < n) {
         w = depo_window(depos[d], P);
-        const bool ok = (w.status == 0);
+        ok = (w.status == 0);
         meta[4 * d + 0] = ok ? w.lo_p : 0;
         meta[4 * d + 1] = ok ? w.lo_t : 0;
         meta[4 * d + 2] = ok ? w.n_p : 0;
@@ -545,11 +550,30 @@ __global__ __launch_bounds__(256) void k_patch_sizes(const wcsim_depo *depos, in
     if (m) {
         int base = 0;
         if (lane == 0)
-            base = atomicAdd(nlarge, __popcll(m));
+            base = atomicAdd(&sums->nlarge, __popcll(m));
         base = __builtin_amdgcn_readlane(base, 0);
         if (big)
             large[base + __popcll(m & lanemask_lt(lane))] = (int32_t)d;
     }
+    // Groups of neighbours whose patches' bounding box fits the region, less those
+    // whose does not, over every eighth workgroup (all of them on the one counter
+    // cost 4 us for 100,000 depos).
+    if (blockIdx.x & 7)
+        return;
+    int rlo = ok ? max(w.lo_p, 0) : INT_MAX, rhi = ok ? min(w.lo_p + w.n_p, P.Np) : 0;
+    int clo = ok ? max(w.lo_t, 0) : INT_MAX, chi = ok ? min(w.lo_t + w.n_t, P.Nt) : 0;
+#pragma unroll
+    for (int k = 1; k < kCloseDepos; k <<= 1) {
+        rlo = min(rlo, __shfl_xor(rlo, k, 64));
+        rhi = max(rhi, __shfl_xor(rhi, k, 64));
+        clo = min(clo, __shfl_xor(clo, k, 64));
+        chi = max(chi, __shfl_xor(chi, k, 64));
+    }
+    const bool first = (lane & (kCloseDepos - 1)) == 0 && rlo < rhi && clo < chi;
+    const bool fits = (int64_t)(rhi - rlo) * (chi - clo) <= kScatCells;
+    const int close = __syncthreads_count(first && fits), apart = __syncthreads_count(first && !fits);
+    if (threadIdx.x == 0 && close != apart)
+        atomicAdd(&sums->close, close - apart);
 }
 
 template <int NT>
@@ -697,49 +721,61 @@ __global__ __launch_bounds__(NT) void k_patch_generic(EventCtx e0, BatchTables b
 __device__ __forceinline__ int div_small(int a, int m) { return (int)(__umul24(a, m) >> 20); }
 __device__ __forceinline__ int magic_small(int b) { return ((1 << 20) + b - 1) / b; }
 
-// Flat patch set -> grid.  A wavefront takes kScatPatches consecutive patches.
-// Depos that follow one another mostly lie on one track and their patches share
-// cells: when the patches' bounding box fits its LDS region the wavefront sums
-// them there, one patch at a time (a patch's cells are distinct, and a
-// wavefront's LDS accesses complete in order), and adds each touched cell to the
-// grid once.  Patches that lie apart go to the grid bin by bin.  Bound by the
-// rate of float atomics: 15.5 M bins of 100,000 track patches 157 -> 41 us.
-constexpr int kScatPatches = 16, kScatCells = 1536, kScatRegs = 4;
+// Flat patch set -> grid, bound by the rate of float atomics.  A wavefront takes `per`
+// consecutive patches.  Plain: one patch, added bin by bin.  SUM: depos that follow
+// one another mostly lie on one track and their patches share cells: when the bounding
+// box of the wavefront's patches fits its LDS region it sums them there, one patch at a
+// time (a patch's cells are distinct, and a wavefront's LDS accesses complete in
+// order), and adds each touched cell to the grid once; patches that lie apart go to
+// the grid bin by bin all the same.
+// SUM is for sets of kScatMany depos or more most of whose neighbours lie together
+// (k_patch_sizes counts that over 256 of each 2,048: PatchSums::close); `per` doubles from 4 to 16 while
+// kScatFill wavefronts remain.  Plain / SUM with 4, 8, 16: tracks, 3,000 depos 9.6 / 8.1,
+// 9.5, 17 us, 6,000 15 / 9.1, 11, 20, 30,000 57 / 21, 18, 28, 60,000 113 / 37, 31, 35,
+// 100,000 174 / 56, 42, 41; uniform depos, 1,000 7.6 / 8.7, 13, 22, 30,000 44 / 47, 47,
+// 48, 100,000 139 / 142, 143, 145; uniform with windows of 1,500 bins, 10,000 92 / 97,
+// 114, 154.  (The workgroup's four wavefronts on one region by LDS atomics: 100,000
+// track depos 95 us.)
+constexpr int64_t kScatMany = 4096, kScatFill = 12288;
+constexpr int kScatRegs = 4;
+// wavefronts a workgroup
+template <bool SUM>
+constexpr int kScatWaves = SUM ? 1 : 4;
 
-__global__ __launch_bounds__(64) void k_scatter_flat(int64_t n, const int32_t *__restrict__ meta,
-                                                     const int64_t *__restrict__ offsets,
-                                                     const float *__restrict__ values, float *grid,
-                                                     int Np, int Nt)
+template <bool SUM>
+__global__ __launch_bounds__(64 * kScatWaves<SUM>) void k_scatter_flat(
+    int64_t n, int per, const int32_t *__restrict__ meta, const int64_t *__restrict__ offsets,
+    const float *__restrict__ values, float *grid, int Np, int Nt)
 {
-    __shared__ float acc[kScatCells];
-    const int lane = threadIdx.x;
-    const int64_t d0 = blockIdx.x * (int64_t)kScatPatches;
-    const int K = (int)min((int64_t)kScatPatches, n - d0);
+    __shared__ float acc[SUM ? kScatCells : 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t d0 = (blockIdx.x * (int64_t)kScatWaves<SUM> + wave) * per;
+    if (d0 >= n)
+        return;
+    const int K = (int)min((int64_t)per, n - d0);
     int4 win = make_int4(0, 0, 0, 0);
     int64_t off = 0;
     if (lane < K) {
         win = *(const int4 *)(meta + 4 * (d0 + lane));
         off = offsets[d0 + lane];
     }
-    // bounding box of the chunk's cells inside the grid
-    const bool some = win.z > 0 && win.w > 0;
-    int rlo = some ? max(win.x, 0) : INT_MAX, rhi = some ? min(win.x + win.z, Np) : INT_MIN;
-    int clo = some ? max(win.y, 0) : INT_MAX, chi = some ? min(win.y + win.w, Nt) : INT_MIN;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        rlo = min(rlo, __shfl_xor(rlo, m, 64));
-        rhi = max(rhi, __shfl_xor(rhi, m, 64));
-        clo = min(clo, __shfl_xor(clo, m, 64));
-        chi = max(chi, __shfl_xor(chi, m, 64));
+    int rlo = 0, clo = 0, W = 1, cells = 0;  // the LDS region (cells = 0: none)
+    if (SUM) {
+        // bounding box of the patches' cells inside the grid
+        const bool some = win.z > 0 && win.w > 0;
+        rlo = wave_max_i<true>(some ? max(win.x, 0) : INT_MAX);
+        clo = wave_max_i<true>(some ? max(win.y, 0) : INT_MAX);
+        const int rhi = wave_max_i<false>(some ? min(win.x + win.z, Np) : INT_MIN);
+        const int chi = wave_max_i<false>(some ? min(win.y + win.w, Nt) : INT_MIN);
+        if (rlo >= rhi || clo >= chi)
+            return;  // every patch is empty or outside the grid
+        const int64_t w64 = (int64_t)chi - clo, cells64 = w64 * ((int64_t)rhi - rlo);
+        W = (int)w64;
+        cells = (int)(cells64 <= kScatCells ? cells64 : 0);
+        for (int x = lane; x < cells; x += 64)
+            acc[x] = 0.0f;
+        wave_lds_sync();
     }
-    if (rlo >= rhi || clo >= chi)
-        return;  // every patch is empty or outside the grid
-    const int64_t W64 = (int64_t)chi - clo, cells64 = W64 * ((int64_t)rhi - rlo);
-    const bool staged = cells64 <= kScatCells;
-    const int W = (int)W64, cells = (int)(staged ? cells64 : 0);
-    for (int x = lane; x < cells; x += 64)
-        acc[x] = 0.0f;
-    wave_lds_sync();
     for (int k = 0; k < K; ++k) {
         const int lo_p = __builtin_amdgcn_readlane(win.x, k), lo_t = __builtin_amdgcn_readlane(win.y, k);
         const int n_p = __builtin_amdgcn_readlane(win.z, k), n_t = __builtin_amdgcn_readlane(win.w, k);
@@ -762,16 +798,17 @@ __global__ __launch_bounds__(64) void k_scatter_flat(int64_t n, const int32_t *_
                 const int i = small ? div_small(it, magic) : it / n_t, j = it - i * n_t;
                 const int I = lo_p + i, J = lo_t + j;
                 if ((unsigned)I < (unsigned)Np && (unsigned)J < (unsigned)Nt) {
-                    if (staged)
+                    if (SUM && cells > 0)
                         acc[(I - rlo) * W + (J - clo)] += x[u];
                     else
                         unsafeAtomicAdd(grid + (size_t)I * Nt + J, x[u]);
                 }
             }
         }
+        if (SUM)
+            wave_lds_sync();  // the next patch may cover the same cells
     }
-    wave_lds_sync();
-    for (int x = lane; x < cells; x += 64) {
+    for (int x = lane; SUM && x < cells; x += 64) {
         const float v = acc[x];
         const int r = x / W;
         if (v != 0.0f)
@@ -2378,11 +2415,11 @@ hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hi
 hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                               int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s)
 {
-    int32_t *nlarge = (int32_t *)(sizes + n + 1);
-    hipLaunchKernelGGL(k_fill_zero1, dim3(1), dim3(16), 0, s, (unsigned char *)nlarge,
-                       sizeof(int64_t));
+    PatchSums *sums = (PatchSums *)(sizes + n + 1);
+    static_assert(sizeof(PatchSums) <= 16, "cleared by one small workgroup");
+    hipLaunchKernelGGL(k_fill_zero1, dim3(1), dim3(16), 0, s, (unsigned char *)sums, sizeof(PatchSums));
     hipLaunchKernelGGL(k_patch_sizes, dim3(blocks_for(std::max<int64_t>(n, 1), 256)), dim3(256), 0,
-                       s, depos, n, pl->kp, meta, sizes, large, nlarge);
+                       s, depos, n, pl->kp, meta, sizes, large, sums);
     return hipGetLastError();
 }
 
@@ -2419,13 +2456,19 @@ hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, i
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *meta,
+hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, bool close, const int32_t *meta,
                                const int64_t *offsets, const float *values, float *grid,
                                hipStream_t s)
 {
     if (n <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_scatter_flat, dim3(blocks_for(n, kScatPatches)), dim3(64), 0, s, n, meta,
+    const bool sum = close && n >= kScatMany;
+    int per = sum ? 4 : 1;
+    while (sum && per < 16 && n >= per * kScatFill)
+        per *= 2;
+    const int waves = sum ? kScatWaves<true> : kScatWaves<false>;
+    auto *kernel = sum ? k_scatter_flat<true> : k_scatter_flat<false>;
+    hipLaunchKernelGGL(kernel, dim3(blocks_for(n, waves * per)), dim3(64 * waves), 0, s, n, per, meta,
                        offsets, values, grid, (int)pl->Np, (int)pl->Nt);
     return hipGetLastError();
 }

@@ -232,7 +232,8 @@ struct wcsim_patches {
     int64_t n;
     int64_t nvalues;
     int32_t *meta;     // [n][4], in buf[0]
-    int64_t *offsets;  // [n+1] and the number of large patches, in buf[0]
+    int64_t *offsets;  // [n+1], then a wcs::PatchSums, in buf[0]
+    bool close;        // most neighbours lie together (PatchSums::close)
     float *values;     // buf[1]
     int device;
     wcs_patch_buffers::Buffer buf[2];
@@ -260,19 +261,24 @@ hipError_t launch_philox(const uint32_t *ctr, const uint32_t *key, int64_t n, ui
                          hipStream_t s);
 
 // unfused rasterize: per-depo sizes, scan, values
-// `sizes` holds n + 2 words: the last one receives the number of patches listed in
-// `large` (n words), those that launch_patch_values draws by a workgroup each.
+// What the host reads with a patch set's total.
+struct PatchSums {
+    int32_t nlarge;  // patches listed in `large`
+    int32_t close;   // of a sample, groups of neighbouring patches that lie together, less the others
+};
+// `sizes` holds n + 2 words: a PatchSums in the last one.  `large` (n words): the
+// patches that launch_patch_values draws by a workgroup each.
 hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                               int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s);
 size_t scan_scratch_bytes(int64_t n);
 hipError_t launch_exclusive_scan_i64(int64_t *data, int64_t n, void *scratch, hipStream_t s);
 hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hipStream_t s);
-// `count`: *nlarge, as the host has read it
+// `nlarge`: PatchSums::nlarge on the device, `count`: as the host has read it
 hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                                uint64_t event_id, const int64_t *offsets, float *values,
                                const int32_t *large, const int32_t *nlarge, int64_t count,
                                hipStream_t s);
-hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, const int32_t *meta,
+hipError_t launch_scatter_flat(const wcsim_plane *pl, int64_t n, bool close, const int32_t *meta,
                                const int64_t *offsets, const float *values, float *grid,
                                hipStream_t s);
 
