@@ -233,9 +233,10 @@ wcsim_status wcsim_patches_device(const wcsim_patches *patches, const int32_t **
 wcsim_status wcsim_patches_copy_to_host(const wcsim_patches *patches, int32_t *meta,
                                         int64_t *offsets, float *values);
 
-/* Destroy a patch set (synchronises the device first).  Its plane may keep the
- * set's two device buffers, of up to 256 MiB each, for its next set; they are
- * released with the plane and the last of its patch sets. */
+/* Destroy a patch set (synchronises the device first).  The library may keep its
+ * two device buffers for the next set of any plane of the device: at most four
+ * buffers and 256 MiB per device, released with the last plane and patch set of
+ * the device, and when an allocation of the library finds no memory. */
 void wcsim_patches_destroy(wcsim_patches *patches);
 
 /* Scatter-Add (Sec. 2 step 2): grid[p][t] += patch value for every patch bin

@@ -12,7 +12,8 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 SRC = [os.path.join(PKG, "csrc", f) for f in ("api.hip", "raster.hip", "fft.hip")]
-HDR = [os.path.join(ROOT, "include", "wcsim.h"), os.path.join(PKG, "csrc", "wcsim_internal.h")]
+HDR = [os.path.join(ROOT, "include", "wcsim.h"), os.path.join(PKG, "csrc", "wcsim_internal.h"),
+       os.path.join(PKG, "csrc", "buffer_pool.h")]
 LIB = os.path.join(PKG, "libwcsim.so")
 
 HIPCC_FLAGS = [

@@ -33,63 +33,6 @@ struct wcs_spectrum {
     }
 };
 
-wcs_patch_buffers::~wcs_patch_buffers()
-{
-    for (Buffer &b : kept)
-        (void)hipFree(b.ptr);
-}
-
-// A kept buffer of the current device that is large enough, but not four times
-// too large, else a new one (once more without the kept ones when memory is out).
-hipError_t wcs_patch_buffers::take(int kind, size_t bytes, Buffer *out)
-{
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess)
-        return e;
-    {
-        std::lock_guard<std::mutex> hold(lock);
-        Buffer &k = kept[kind];
-        if (k.ptr && k.device == dev && k.bytes >= bytes && k.bytes / 4 <= bytes) {
-            *out = k;
-            k = Buffer{};
-            return hipSuccess;
-        }
-    }
-    *out = Buffer{};
-    e = hipMalloc(&out->ptr, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        std::lock_guard<std::mutex> hold(lock);
-        for (Buffer &b : kept) {
-            (void)hipFree(b.ptr);
-            b = Buffer{};
-        }
-        e = hipMalloc(&out->ptr, bytes);
-    }
-    if (e != hipSuccess) {
-        *out = Buffer{};
-        return e;
-    }
-    out->bytes = bytes;
-    out->device = dev;
-    return hipSuccess;
-}
-
-void wcs_patch_buffers::give(int kind, Buffer *b)
-{
-    Buffer old = *b;
-    *b = Buffer{};
-    int dev = -1;
-    // (the synchronised device is the current one; hipFree waits for another)
-    if (old.ptr && old.bytes <= kMaxBytes && hipGetDevice(&dev) == hipSuccess &&
-        dev == old.device) {
-        std::lock_guard<std::mutex> hold(lock);
-        std::swap(old, kept[kind]);  // the newest stays: sets of one plane are of a size
-    }
-    (void)hipFree(old.ptr);
-}
-
 namespace wcs {
 
 namespace {
@@ -111,6 +54,21 @@ wcsim_status check_hip(hipError_t e, const char *what)
 }
 
 namespace {
+
+// The pool of a device, while a plane or patch set of it lives.
+constexpr int kMaxDevices = 64;
+std::shared_ptr<wcs_pool> pool_of(int device)
+{
+    static std::mutex lock;
+    static std::weak_ptr<wcs_pool> pools[kMaxDevices];
+    if (device < 0 || device >= kMaxDevices)
+        return std::make_shared<wcs_pool>();
+    std::lock_guard<std::mutex> hold(lock);
+    std::shared_ptr<wcs_pool> p = pools[device].lock();
+    if (!p)
+        pools[device] = p = std::make_shared<wcs_pool>();
+    return p;
+}
 
 bool finite_all(std::initializer_list<double> v)
 {
@@ -304,10 +262,16 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
     return WCSIM_OK;
 }
 
-template <typename T>
-wcsim_status upload(T **dst, const std::vector<T> &src, hipStream_t s)
+// Device memory of a plane; the idle buffers of its device make room for it.
+hipError_t plane_malloc(const wcsim_plane *pl, void **ptr, size_t bytes)
 {
-    WCS_HIP(hipMalloc((void **)dst, sizeof(T) * src.size()));
+    return (hipError_t)pl->pool->alloc(ptr, bytes);
+}
+
+template <typename T>
+wcsim_status upload(const wcsim_plane *pl, T **dst, const std::vector<T> &src, hipStream_t s)
+{
+    WCS_HIP(plane_malloc(pl, (void **)dst, sizeof(T) * src.size()));
     WCS_HIP(hipMemcpyAsync(*dst, src.data(), sizeof(T) * src.size(), hipMemcpyHostToDevice, s));
     return WCSIM_OK;
 }
@@ -326,11 +290,11 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     wcsim_plane *pl = new (std::nothrow) wcsim_plane();
     if (!pl)
         return fail(WCSIM_E_NOMEM, "host allocation failed");
-    pl->patch_buffers = std::make_shared<wcs_patch_buffers>();
     pl->desc = *desc;
     pl->desc.response = nullptr;
     pl->phys = *phys;
     (void)hipGetDevice(&pl->device);
+    pl->pool = pool_of(pl->device);
     pl->Np = (int64_t)desc->nwires * desc->nimpact;
     pl->Nt = desc->nticks;
     pl->Nw = desc->nwires;
@@ -412,11 +376,11 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     spec->F = pl->F;
     spec->device = pl->device;
     spec->poly = pl->poly;
-    if ((st = upload(&spec->twT, twiddles(pl->N2, pl->N2), s)) != WCSIM_OK ||
-        (st = upload(&spec->twHalf, twiddles(pl->Nfft, pl->N2 + 1), s)) != WCSIM_OK ||
-        (st = upload(&spec->twL, twiddles(pl->L, pl->L), s)) != WCSIM_OK ||
-        (pl->fold && (st = upload(&spec->twF, twiddles(pl->L10, pl->L10), s)) != WCSIM_OK) ||
-        (pl->poly && (st = upload(&spec->twP, twiddles(poly_block_rows(), poly_block_rows()), s)) !=
+    if ((st = upload(pl, &spec->twT, twiddles(pl->N2, pl->N2), s)) != WCSIM_OK ||
+        (st = upload(pl, &spec->twHalf, twiddles(pl->Nfft, pl->N2 + 1), s)) != WCSIM_OK ||
+        (st = upload(pl, &spec->twL, twiddles(pl->L, pl->L), s)) != WCSIM_OK ||
+        (pl->fold && (st = upload(pl, &spec->twF, twiddles(pl->L10, pl->L10), s)) != WCSIM_OK) ||
+        (pl->poly && (st = upload(pl, &spec->twP, twiddles(poly_block_rows(), poly_block_rows()), s)) !=
                          WCSIM_OK))
         return cleanup(st);
     pl->twT = spec->twT;
@@ -426,21 +390,21 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     pl->twP = spec->twP;
     hipError_t e;
     const size_t kbytes = sizeof(float2) * (size_t)pl->C * pl->L * pl->F;
-    if ((e = hipMalloc((void **)&spec->K, kbytes)) != hipSuccess)
+    if ((e = plane_malloc(pl, (void **)&spec->K, kbytes)) != hipSuccess)
         return cleanup(check_hip(e, "hipMalloc(response spectrum)"));
     pl->K = spec->K;
     if (pl->poly) {
         const size_t hbytes =
             sizeof(float2) * (size_t)pl->C * pl->kp.nimpact * poly_block_rows() * pl->F;
-        if ((e = hipMalloc((void **)&spec->H, hbytes)) != hipSuccess)
+        if ((e = plane_malloc(pl, (void **)&spec->H, hbytes)) != hipSuccess)
             return cleanup(check_hip(e, "hipMalloc(polyphase response spectra)"));
         pl->KP = spec->H;
     }
     // device copies: [combined Rp x Rt | caller's Rp x Rt0 | electronics]
     const size_t rbytes = sizeof(float) * (nresp + nresp0 + nelec);
-    if ((e = hipMalloc((void **)&resp, rbytes)) != hipSuccess)
+    if ((e = plane_malloc(pl, (void **)&resp, rbytes)) != hipSuccess)
         return cleanup(check_hip(e, "hipMalloc(response)"));
-    if ((e = hipMalloc(&work, response_work_bytes(pl))) != hipSuccess)
+    if ((e = plane_malloc(pl, &work, response_work_bytes(pl))) != hipSuccess)
         return cleanup(check_hip(e, "hipMalloc(response work)"));
     if (nelec == 0) {
         if ((e = hipMemcpyAsync(resp, desc->response, sizeof(float) * nresp,
@@ -639,8 +603,20 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
     if (!P)
         return fail(WCSIM_E_NOMEM, "host allocation failed");
     P->n = n;
-    P->device = pl->device;
-    P->buffers = pl->patch_buffers;
+    P->device = -1;
+    (void)hipGetDevice(&P->device);
+    P->pooled = P->device == pl->device;
+    P->pool = pl->pool;
+    // (a buffer of another device than the pool's is neither taken from it nor kept)
+    auto get = [&](int k, size_t bytes) {
+        if (P->pooled)
+            return (hipError_t)P->pool->take(bytes, &P->buf[k]);
+        const hipError_t r = hipMalloc(&P->buf[k].ptr, bytes);
+        P->buf[k].bytes = bytes;
+        if (r != hipSuccess)
+            P->buf[k] = wcs_pool::Buffer{};
+        return r;
+    };
     auto bail = [&](wcsim_status r) {
         if (r != WCSIM_OK)
             wcsim_patches_destroy(P);
@@ -657,7 +633,7 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
     const size_t off_list = off_scan + align_up(scan_scratch_bytes(n + 1));
     const size_t off_depos = off_list + align_up(sizeof(int32_t) * nn);
     const size_t bytes = off_depos + (mem == WCSIM_MEM_HOST ? sizeof(wcsim_depo) * nn : 0);
-    if ((e = P->buffers->take(0, bytes, &P->buf[0])) != hipSuccess)
+    if ((e = get(0, bytes)) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch set)"));
     char *base = (char *)P->buf[0].ptr;
     P->meta = (int32_t *)base;
@@ -685,8 +661,7 @@ wcsim_status wcsim_rasterize(const wcsim_plane *pl, const wcsim_depo *depos, int
         return bail(check_hip(e, "patch total"));
     P->nvalues = sums.total;
     P->close = sums.more.close >= 0;
-    if ((e = P->buffers->take(1, sizeof(float) * (size_t)std::max<int64_t>(P->nvalues, 1),
-                              &P->buf[1])) != hipSuccess)
+    if ((e = get(1, sizeof(float) * (size_t)std::max<int64_t>(P->nvalues, 1))) != hipSuccess)
         return bail(check_hip(e, "hipMalloc(patch values)"));
     P->values = (float *)P->buf[1].ptr;
     if ((e = launch_patch_values(pl, dd, n, event_id, P->offsets, P->values, list,
@@ -743,9 +718,12 @@ void wcsim_patches_destroy(wcsim_patches *P)
 {
     if (!P)
         return;
-    (void)hipDeviceSynchronize();
-    for (int k = 0; k < 2; ++k)
-        P->buffers->give(k, &P->buf[k]);
+    // (the device that is waited for is the current one)
+    int dev = -1;
+    const bool idle = hipDeviceSynchronize() == hipSuccess && P->pooled &&
+                      hipGetDevice(&dev) == hipSuccess && dev == P->device;
+    for (wcs_pool::Buffer &b : P->buf)
+        P->pool->give(&b, idle);
     delete P;
 }
 
@@ -928,7 +906,6 @@ constexpr size_t kScratchSlack = 512u << 10;
 static __device__ __align__(256) unsigned char scratch[WCSIM_NOALLOC_SCRATCH_BYTES + kScratchSlack];
 
 namespace {
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void *g_scratch_ptr[kMaxDevices];  // device address of `scratch` per device (nullptr: not yet)
 
@@ -1009,8 +986,8 @@ wcsim_status wcsim_tune_schedules(const wcsim_plane_desc *desc, const wcsim_phys
             continue;  // not a valid schedule for this plane
         const int64_t nout = (out_kind == WCSIM_OUT_WIRE) ? pl->Nw : pl->Np;
         void *ws = nullptr, *out = nullptr;
-        if (hipMalloc(&ws, wcsim_simulate_workspace_bytes(pl, n, out_kind)) != hipSuccess ||
-            hipMalloc(&out, sizeof(float) * (size_t)nout * pl->Nt) != hipSuccess) {
+        if (plane_malloc(pl, &ws, wcsim_simulate_workspace_bytes(pl, n, out_kind)) != hipSuccess ||
+            plane_malloc(pl, &out, sizeof(float) * (size_t)nout * pl->Nt) != hipSuccess) {
             result = fail(WCSIM_E_NOMEM, "device allocation failed while tuning");
         } else {
             std::vector<float> t;

@@ -6,10 +6,10 @@
 #include <stdint.h>
 
 #include <memory>
-#include <mutex>
 #include <string>
 #include <vector>
 
+#include "buffer_pool.h"
 #include "wcsim.h"
 
 namespace wcs {
@@ -158,26 +158,24 @@ TileShape tile_shape(int id);
 }  // namespace wcs
 
 // ---------------------------------------------------------------------------
-// Device buffers of destroyed patch sets, kept for the next one of the same
-// plane: an allocation and a release cost 0.1-0.5 ms each, more than the
-// kernels of a 100,000-depo set.  At most one buffer of each kind and kMaxBytes
-// each; shared by the plane and its patch sets, released with the last of them.
-// A buffer comes back only after its patch set's destruction has synchronised
-// the device, so whoever takes it next may use it on any stream.
+// Device buffers of destroyed patch sets, kept for the next one: an allocation
+// and a release cost 0.1-0.5 ms each, more than the kernels of a 100,000-depo set.
+// One pool per device, shared by its planes and patch sets and released with the
+// last of them; the library's own allocations that find no memory empty it and try
+// again.
 // ---------------------------------------------------------------------------
-struct wcs_patch_buffers {
-    static constexpr size_t kMaxBytes = (size_t)256 << 20;
-    struct Buffer {
-        void *ptr = nullptr;
-        size_t bytes = 0;
-        int device = -1;
-    };
-    std::mutex lock;
-    Buffer kept[2];  // [0] windows, offsets and scratch, [1] values
-    ~wcs_patch_buffers();
-    hipError_t take(int kind, size_t bytes, Buffer *out);
-    void give(int kind, Buffer *b);  // (device idle)
+struct wcs_hip_memory {
+    static int alloc(void **ptr, size_t bytes)
+    {
+        const hipError_t e = hipMalloc(ptr, bytes);
+        if (e == hipErrorOutOfMemory)
+            (void)hipGetLastError();
+        return (int)e;
+    }
+    static bool out_of_memory(int e) { return e == (int)hipErrorOutOfMemory; }
+    static void free(void *ptr) { (void)hipFree(ptr); }
 };
+using wcs_pool = wcs::BufferPool<wcs_hip_memory>;
 
 // ---------------------------------------------------------------------------
 // Plane object
@@ -220,7 +218,7 @@ struct wcsim_plane {
     // owner of K and the twiddle tables; planes with the same response and
     // transform sizes share one
     std::shared_ptr<struct wcs_spectrum> spectrum;
-    std::shared_ptr<struct wcs_patch_buffers> patch_buffers;
+    std::shared_ptr<wcs_pool> pool;  // of `device`
     int tile;
     bool det;  // reproducible sums: sorted tile lists, owner flush, ordered large patches
     wcs::TileShape ts;
@@ -235,9 +233,10 @@ struct wcsim_patches {
     int64_t *offsets;  // [n+1], then a wcs::PatchSums, in buf[0]
     bool close;        // most neighbours lie together (PatchSums::close)
     float *values;     // buf[1]
-    int device;
-    wcs_patch_buffers::Buffer buf[2];
-    std::shared_ptr<wcs_patch_buffers> buffers;
+    int device;  // of the buffers
+    bool pooled;  // the buffers are of the pool's device
+    wcs_pool::Buffer buf[2];
+    std::shared_ptr<wcs_pool> pool;
 };
 
 namespace wcs {
