@@ -39,7 +39,28 @@ namespace {
 thread_local std::string g_last_error;
 }
 
-void set_error(const std::string &msg) { g_last_error = msg; }
+// (an empty message where there is no memory for it)
+void set_error(const std::string &msg) noexcept
+{
+    try {
+        g_last_error = msg;
+    } catch (...) {
+        g_last_error.clear();
+    }
+}
+
+// `body` of an entry point: a C++ exception becomes a status.
+template <class F>
+wcsim_status guarded(F body) noexcept
+{
+    try {
+        return body();
+    } catch (...) {  // (nothing here throws but the host's allocator)
+        g_last_error.clear();
+        g_last_error.append("no host memory");  // short: held without an allocation
+        return WCSIM_E_NOMEM;
+    }
+}
 
 wcsim_status fail(wcsim_status st, const std::string &msg)
 {
@@ -287,9 +308,8 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     if (st != WCSIM_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
-    wcsim_plane *pl = new (std::nothrow) wcsim_plane();
-    if (!pl)
-        return fail(WCSIM_E_NOMEM, "host allocation failed");
+    std::unique_ptr<wcsim_plane> plane(new wcsim_plane());
+    wcsim_plane *pl = plane.get();
     pl->desc = *desc;
     pl->desc.response = nullptr;
     pl->phys = *phys;
@@ -325,10 +345,8 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     k.pad_ = 0;
     k.tau = phys->lifetime;
     k.accel = phys->drift_accel;
-    if ((st = choose_schedule(pl, sched, donor)) != WCSIM_OK) {
-        free_plane(pl);
+    if ((st = choose_schedule(pl, sched, donor)) != WCSIM_OK)
         return st;
-    }
     // the caller's response and electronics response; the plane convolves
     // with their combination, Rp x Rt (effective) built on the device
     const size_t nresp0 = (size_t)pl->Rp * desc->resp_nticks;
@@ -350,19 +368,14 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
             pl->twF = d.twF;
             pl->KP = d.H;
             pl->twP = d.twP;
-            *out = pl;
+            *out = plane.release();
             return WCSIM_OK;
         }
     }
-    float *resp = nullptr;
-    void *work = nullptr;
-    auto cleanup = [&](wcsim_status r) {
-        (void)hipFree(resp);
-        (void)hipFree(work);
-        if (r != WCSIM_OK)
-            free_plane(pl);
-        return r;
-    };
+    struct DeviceTemp {
+        void *p = nullptr;
+        ~DeviceTemp() { (void)hipFree(p); }
+    } resp_mem, work_mem;
     auto spec = std::make_shared<wcs_spectrum>();
     pl->spectrum = spec;
     spec->response.assign(desc->response, desc->response + nresp0);
@@ -382,7 +395,7 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
         (pl->fold && (st = upload(pl, &spec->twF, twiddles(pl->L10, pl->L10), s)) != WCSIM_OK) ||
         (pl->poly && (st = upload(pl, &spec->twP, twiddles(poly_block_rows(), poly_block_rows()), s)) !=
                          WCSIM_OK))
-        return cleanup(st);
+        return st;
     pl->twT = spec->twT;
     pl->twHalf = spec->twHalf;
     pl->twL = spec->twL;
@@ -391,42 +404,43 @@ wcsim_status plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phy
     hipError_t e;
     const size_t kbytes = sizeof(float2) * (size_t)pl->C * pl->L * pl->F;
     if ((e = plane_malloc(pl, (void **)&spec->K, kbytes)) != hipSuccess)
-        return cleanup(check_hip(e, "hipMalloc(response spectrum)"));
+        return check_hip(e, "hipMalloc(response spectrum)");
     pl->K = spec->K;
     if (pl->poly) {
         const size_t hbytes =
             sizeof(float2) * (size_t)pl->C * pl->kp.nimpact * poly_block_rows() * pl->F;
         if ((e = plane_malloc(pl, (void **)&spec->H, hbytes)) != hipSuccess)
-            return cleanup(check_hip(e, "hipMalloc(polyphase response spectra)"));
+            return check_hip(e, "hipMalloc(polyphase response spectra)");
         pl->KP = spec->H;
     }
     // device copies: [combined Rp x Rt | caller's Rp x Rt0 | electronics]
     const size_t rbytes = sizeof(float) * (nresp + nresp0 + nelec);
-    if ((e = plane_malloc(pl, (void **)&resp, rbytes)) != hipSuccess)
-        return cleanup(check_hip(e, "hipMalloc(response)"));
-    if ((e = plane_malloc(pl, &work, response_work_bytes(pl))) != hipSuccess)
-        return cleanup(check_hip(e, "hipMalloc(response work)"));
+    if ((e = plane_malloc(pl, &resp_mem.p, rbytes)) != hipSuccess)
+        return check_hip(e, "hipMalloc(response)");
+    if ((e = plane_malloc(pl, &work_mem.p, response_work_bytes(pl))) != hipSuccess)
+        return check_hip(e, "hipMalloc(response work)");
+    float *resp = (float *)resp_mem.p;
     if (nelec == 0) {
         if ((e = hipMemcpyAsync(resp, desc->response, sizeof(float) * nresp,
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
-            return cleanup(check_hip(e, "hipMemcpyAsync(response)"));
+            return check_hip(e, "hipMemcpyAsync(response)");
     } else {
         float *r0d = resp + nresp, *ed = r0d + nresp0;
         if ((e = hipMemcpyAsync(r0d, desc->response, sizeof(float) * nresp0,
                                 hipMemcpyHostToDevice, s)) != hipSuccess ||
             (e = hipMemcpyAsync(ed, desc->elec_response, sizeof(float) * nelec,
                                 hipMemcpyHostToDevice, s)) != hipSuccess)
-            return cleanup(check_hip(e, "hipMemcpyAsync(response)"));
+            return check_hip(e, "hipMemcpyAsync(response)");
         if ((e = launch_combine_response(r0d, pl->Rp, desc->resp_nticks, ed, (int)nelec, resp,
                                          s)) != hipSuccess)
-            return cleanup(check_hip(e, "combined response"));
+            return check_hip(e, "combined response");
     }
-    if ((e = build_response_spectrum(pl, resp, work, s)) != hipSuccess)
-        return cleanup(check_hip(e, "response spectrum"));
+    if ((e = build_response_spectrum(pl, resp, work_mem.p, s)) != hipSuccess)
+        return check_hip(e, "response spectrum");
     if ((e = hipStreamSynchronize(s)) != hipSuccess)
-        return cleanup(check_hip(e, "hipStreamSynchronize"));
-    *out = pl;
-    return cleanup(WCSIM_OK);
+        return check_hip(e, "hipStreamSynchronize");
+    *out = plane.release();
+    return WCSIM_OK;
 }
 
 // Host-side checks of host depos: finite fields, q >= 0, x >= plane_x, a depo
@@ -473,7 +487,7 @@ const char *wcsim_last_error(void) { return g_last_error.c_str(); }
 wcsim_status wcsim_plane_create(const wcsim_plane_desc *desc, const wcsim_physics *phys,
                                 void *stream, wcsim_plane **out)
 {
-    return plane_create(desc, phys, nullptr, nullptr, stream, out);
+    return guarded([&] { return plane_create(desc, phys, nullptr, nullptr, stream, out); });
 }
 
 wcsim_status wcsim_plane_create_with_schedule(const wcsim_plane_desc *desc,
@@ -481,7 +495,7 @@ wcsim_status wcsim_plane_create_with_schedule(const wcsim_plane_desc *desc,
                                               const wcsim_schedule *sched, void *stream,
                                               wcsim_plane **out)
 {
-    return plane_create(desc, phys, sched, nullptr, stream, out);
+    return guarded([&] { return plane_create(desc, phys, sched, nullptr, stream, out); });
 }
 
 wcsim_status wcsim_plane_create_sharing(const wcsim_plane_desc *desc, const wcsim_physics *phys,
@@ -498,8 +512,8 @@ wcsim_status wcsim_plane_create_sharing(const wcsim_plane_desc *desc, const wcsi
     sc.deterministic = donor->det ? 1 : 0;
     // the donor's transform may be too short for a longer readout
     if (desc && donor->Nfft < desc->nticks + effective_resp_nticks(desc) - 1)
-        return plane_create(desc, phys, nullptr, nullptr, stream, out);
-    return plane_create(desc, phys, &sc, donor, stream, out);
+        return guarded([&] { return plane_create(desc, phys, nullptr, nullptr, stream, out); });
+    return guarded([&] { return plane_create(desc, phys, &sc, donor, stream, out); });
 }
 
 void wcsim_plane_destroy(wcsim_plane *plane)
@@ -982,7 +996,7 @@ wcsim_status wcsim_tune_schedules(const wcsim_plane_desc *desc, const wcsim_phys
     for (int32_t i = 0; i < ncand && result == WCSIM_OK; ++i) {
         ms[i] = -1.0f;
         wcsim_plane *pl = nullptr;
-        if (plane_create(desc, phys, &cands[i], nullptr, stream, &pl) != WCSIM_OK)
+        if (wcsim_plane_create_with_schedule(desc, phys, &cands[i], stream, &pl) != WCSIM_OK)
             continue;  // not a valid schedule for this plane
         const int64_t nout = (out_kind == WCSIM_OUT_WIRE) ? pl->Nw : pl->Np;
         void *ws = nullptr, *out = nullptr;

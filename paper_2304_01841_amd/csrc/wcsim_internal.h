@@ -17,7 +17,7 @@ namespace wcs {
 // ---------------------------------------------------------------------------
 // Status plumbing
 // ---------------------------------------------------------------------------
-void set_error(const std::string &msg);
+void set_error(const std::string &msg) noexcept;
 wcsim_status fail(wcsim_status st, const std::string &msg);
 wcsim_status check_hip(hipError_t e, const char *what);
 
