@@ -173,11 +173,6 @@ std::vector<float2> twiddles(int n, int count)
     return t;
 }
 
-void free_plane(wcsim_plane *p)
-{
-    delete p;  // device buffers belong to the (possibly shared) spectrum
-}
-
 constexpr size_t kLdsBytes = 160 * 1024;
 
 wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wcsim_plane *donor)
@@ -188,8 +183,12 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
         return fail(WCSIM_E_INVALID, "fft_ticks must be even and >= nticks + resp_nticks - 1");
     pl->Nfft = nfft;
     pl->N2 = nfft / 2;
-    if (!make_plan(pl->N2, &pl->planT))
+    FftPlan smooth;
+    if (!make_plan(pl->N2, &smooth))
         return fail(WCSIM_E_INVALID, "fft_ticks/2 must factor into 2, 3 and 5");
+    // The documented bound, N' <= 20000: two rows of N' / 2 + 1 values and the tables
+    // within 160 KB.  (Passes A and C hold one row where rows are long; the bound stays
+    // what callers know.)
     if (sizeof(float2) * ((size_t)(pl->N2 + 1) * 2 + twiddle_table_len(pl->N2) +
                           twiddle_table_len(pl->N2 + 1)) > kLdsBytes ||
         twiddle_table_len(pl->N2 + 1) > 256)
@@ -239,11 +238,6 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
             const int R = pl->planL.radix[q];
             if ((int64_t)L / R * pl->Fb > 1024LL * (32 / R))
                 return fail(WCSIM_E_INVALID, "pitch block too large for one workgroup");
-        }
-        for (int q = 0; q < pl->planT.npass; ++q) {
-            const int R = pl->planT.radix[q];
-            if ((int64_t)pl->N2 / R * 2 > 1024LL * (32 / R))
-                return fail(WCSIM_E_INVALID, "tick transform too large for one workgroup");
         }
         if (!make_tick_plan(pl))
             return fail(WCSIM_E_INVALID, "tick transform too large for one workgroup");
@@ -521,7 +515,7 @@ void wcsim_plane_destroy(wcsim_plane *plane)
     if (!plane)
         return;
     (void)hipDeviceSynchronize();
-    free_plane(plane);
+    delete plane;  // device buffers belong to the (possibly shared) spectrum
 }
 
 wcsim_status wcsim_plane_get_info(const wcsim_plane *pl, wcsim_plane_info *info)

@@ -643,9 +643,11 @@ __device__ __forceinline__ void gen_pass_any(float2 *row, const float2 *tab, con
 
 struct FftGen {
     static constexpr int kMaxThreads = 1024;
-    // Wavefronts per SIMD that the register allocation aims at (80 registers):
-    // left alone, the radix-16 passes took 83 to 98 (4 or 5 wavefronts) and 4800
-    // rows of 1600 points 5% longer; at 8 wavefronts longer rows lost that again.
+    // Wavefronts per SIMD that the register allocation aims at (80 registers).  It
+    // binds pass C alone: left to itself its radix-16 passes took 83 to 98 registers (4 or
+    // 5 wavefronts) and 4800 rows of 1600 points 5% longer; held to 80 it spills three
+    // (16 bytes of scratch a lane).  Pass A takes 60 either way.  At 8 wavefronts longer
+    // rows lost that again.
     static constexpr int kMinWaves = 6;
     GenPlan plan;
     template <class Load, class Store>

@@ -2407,11 +2407,6 @@ hipError_t launch_exclusive_scan_i64(int64_t *data, int64_t n, void *scratch, hi
     return exclusive_scan<int64_t>(data, n, scratch, s);
 }
 
-hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hipStream_t s)
-{
-    return exclusive_scan<int32_t>(data, n, scratch, s);
-}
-
 hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                               int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s)
 {

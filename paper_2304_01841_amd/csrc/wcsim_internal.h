@@ -198,7 +198,7 @@ struct wcsim_plane {
     int Fb, L10;
     bool fold;
     int Rp, Rt, r0;
-    wcs::FftPlan planT, planL, planF;
+    wcs::FftPlan planL, planF;
     // general tick-axis transform: plan, threads per row and rows per workgroup
     // of passes A and C (one row for the lengths with a compiled transform)
     wcs::GenPlan planG;
@@ -271,7 +271,6 @@ hipError_t launch_patch_sizes(const wcsim_plane *pl, const wcsim_depo *depos, in
                               int32_t *meta, int64_t *sizes, int32_t *large, hipStream_t s);
 size_t scan_scratch_bytes(int64_t n);
 hipError_t launch_exclusive_scan_i64(int64_t *data, int64_t n, void *scratch, hipStream_t s);
-hipError_t launch_exclusive_scan_i32(int32_t *data, int64_t n, void *scratch, hipStream_t s);
 // `nlarge`: PatchSums::nlarge on the device, `count`: as the host has read it
 hipError_t launch_patch_values(const wcsim_plane *pl, const wcsim_depo *depos, int64_t n,
                                uint64_t event_id, const int64_t *offsets, float *values,
