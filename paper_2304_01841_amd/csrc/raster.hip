@@ -2102,6 +2102,23 @@ TileShape tile_shape(int id)
     }
 }
 
+// Compute units of the current device (cached per device).
+int device_cus()
+{
+    static std::atomic<int> cus[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return 256;
+    int v = cus[dev].load(std::memory_order_relaxed);
+    if (v <= 0) {
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            v <= 0)
+            v = 256;
+        cus[dev].store(v, std::memory_order_relaxed);
+    }
+    return v;
+}
+
 hipError_t launch_fill_zero(void *ptr, size_t bytes, hipStream_t s)
 {
     if (bytes == 0)
@@ -2200,7 +2217,7 @@ hipError_t launch_digitize(const float *wave, int64_t nrows, int64_t ncols, floa
     return hipGetLastError();
 }
 
-// Coloured noise.  A workgroup of T / 8 threads takes T columns of one row: it
+// Coloured noise.  A workgroup of T / 8 threads (or more) takes T columns of one row: it
 // draws the white deviates of those columns and of the 8 ceil(nfir / 8) before
 // them into LDS in FP64 (one Philox call per quad, as k_digitize), then each
 // thread filters eight consecutive columns (FP64 sums in order of the tap),
@@ -2212,12 +2229,23 @@ hipError_t launch_digitize(const float *wave, int64_t nrows, int64_t ncols, floa
 // Taps come by scalar loads; zeros stand for the noise before column 0 and the
 // taps past the last (exact while the taps are finite).  5.76 M samples, 64 taps:
 // 67.7 -> 33.8 us; the deviates alone take 13 us, the FP64 products 12 us.
+// Launches of at most kFirShared workgroups a CU take rows that are not whole groups of
+// eight by kRowsShared, where the single accesses show (960 rows of 1001 columns, one
+// tap 8.6 -> 7.4 us, 400 x 6001 14.3 -> 13.2); in larger ones other workgroups hide them and
+// the exchange's barriers cost more (960 x 3001 15.8 -> 16.9).
 constexpr int kFirPer = 8;
+constexpr int kFirShared = 5;  // workgroups a CU
 constexpr int kFirPad = 4;  // rows of z are 8 k + 4 long: quads are written to all banks
 
 __device__ __forceinline__ int fir_stride(int nz) { return nz / kFirPer / 8 * 8 + 8 + kFirPad; }
 
-template <bool VEC>
+// ROWS: how samples and codes are read and written.  kRowsWhole: rows of whole groups
+// of eight, two 16-byte loads and a 16-byte store a thread.  kRowsShared: any row, the
+// noise exchanged through LDS, neighbouring threads on neighbouring columns.
+// kRowsSingle: any row, eight single accesses a thread and no exchange.
+// MORE: two threads for every eight columns; those past the filter's only draw.
+enum { kRowsWhole, kRowsShared, kRowsSingle };
+template <int ROWS, bool MORE>
 __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ wave, int64_t nrows,
                                                       int64_t ncols, int64_t tiles, float gain,
                                                       float pedestal, float sigma,
@@ -2226,7 +2254,8 @@ __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ 
                                                       uint32_t event, uint16_t *__restrict__ adc)
 {
     extern __shared__ double fir_lds[];
-    const int T = kFirPer * blockDim.x, tid = threadIdx.x;
+    const int T = kFirPer / (MORE ? 2 : 1) * blockDim.x, tid = threadIdx.x;
+    const bool filters = !MORE || tid < T / kFirPer;
     const int nkb = (nfir + kFirPer - 1) / kFirPer;  // blocks of taps
     const int nz = T + kFirPer * nkb, stride = fir_stride(nz);
     double *z = fir_lds;
@@ -2234,6 +2263,26 @@ __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ 
     const int64_t t0 = (blockIdx.x - row * tiles) * T, base = t0 - kFirPer * nkb;
     const int64_t c0 = t0 + kFirPer * tid;  // this thread's first column
     const int64_t i0 = row * ncols + c0;
+    // The samples and the first taps are under way before the draws.
+    float w[kFirPer];
+    if (ROWS == kRowsWhole) {
+        const int64_t i = (filters && c0 < ncols) ? i0 : row * ncols;
+#pragma unroll
+        for (int m = 0; m < kFirPer; m += 4) {
+            const float4 v = *(const float4 *)(wave + i + m);
+            w[m] = v.x;
+            w[m + 1] = v.y;
+            w[m + 2] = v.z;
+            w[m + 3] = v.w;
+        }
+    } else if (ROWS == kRowsShared) {
+#pragma unroll
+        for (int m = 0; m < kFirPer; ++m) {
+            const int c = tid + m * (int)blockDim.x;
+            w[m] = ((!MORE || c < T) && t0 + c < ncols) ? wave[row * ncols + t0 + c] : 0.0f;
+        }
+    }
+    const float tap = fir[min(tid, nfir - 1)];
     for (int qi = tid; 4 * qi < nz; qi += blockDim.x) {
         const int64_t c = base + 4 * qi;  // first column of the quad
         double zz[4] = {0.0, 0.0, 0.0, 0.0};
@@ -2247,8 +2296,8 @@ __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ 
         for (int m = 0; m < 4; ++m)
             z[((4 * qi + m) & (kFirPer - 1)) * stride + (4 * qi + m) / kFirPer] = zz[m];
     }
-    bool bad = false;
-    for (int k = tid; k < nfir; k += blockDim.x)
+    bool bad = !isfinite(tap);
+    for (int k = tid + (int)blockDim.x; k < nfir; k += blockDim.x)
         bad = bad || !isfinite(fir[k]);
     const bool general = __syncthreads_or(bad);
     double n[kFirPer];
@@ -2256,7 +2305,8 @@ __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ 
     for (int m = 0; m < kFirPer; ++m)
         n[m] = 0.0;
     const int pos = nkb + tid;
-    if (!general) {
+    if (!filters) {
+    } else if (!general) {
         // one block of taps t[r]: columns of x (this octet) and y (the one before)
         auto block = [&](const double *t, const double *x, const double *y) {
 #pragma unroll
@@ -2311,45 +2361,42 @@ __global__ __launch_bounds__(256) void k_digitize_fir(const float *__restrict__ 
             }
         }
     }
-    float w[kFirPer];
-#pragma unroll
-    for (int m = 0; m < kFirPer; ++m)
-        w[m] = 0.0f;
-    if (VEC) {
-        if (c0 < ncols) {
-#pragma unroll
-            for (int m = 0; m < kFirPer; m += 4) {
-                const float4 v = *(const float4 *)(wave + i0 + m);
-                w[m] = v.x;
-                w[m + 1] = v.y;
-                w[m + 2] = v.z;
-                w[m + 3] = v.w;
-            }
-        }
-    } else {
+    if (ROWS == kRowsWhole) {
+        if (!filters || c0 >= ncols)
+            return;
+        uint32_t c[kFirPer];
 #pragma unroll
         for (int m = 0; m < kFirPer; ++m)
-            if (c0 + m < ncols)
-                w[m] = wave[i0 + m];
-    }
-    uint16_t c[kFirPer];
-#pragma unroll
-    for (int m = 0; m < kFirPer; ++m)
-        c[m] = adc_code(w[m], gain, pedestal, sigma, (float)n[m], top);
-    if (VEC) {
-        if (c0 < ncols) {
-            uint4 v;
-            v.x = c[0] | (uint32_t)c[1] << 16;
-            v.y = c[2] | (uint32_t)c[3] << 16;
-            v.z = c[4] | (uint32_t)c[5] << 16;
-            v.w = c[6] | (uint32_t)c[7] << 16;
-            *(uint4 *)(adc + i0) = v;
-        }
-    } else {
+            c[m] = adc_code(w[m], gain, pedestal, sigma, (float)n[m], top);
+        *(uint4 *)(adc + i0) = make_uint4(c[0] | c[1] << 16, c[2] | c[3] << 16, c[4] | c[5] << 16,
+                                          c[6] | c[7] << 16);
+    } else if (ROWS == kRowsSingle) {
 #pragma unroll
         for (int m = 0; m < kFirPer; ++m)
-            if (c0 + m < ncols)
-                adc[i0 + m] = c[m];
+            w[m] = (filters && c0 + m < ncols) ? wave[i0 + m] : 0.0f;
+#pragma unroll
+        for (int m = 0; m < kFirPer; ++m)
+            if (filters && c0 + m < ncols)
+                adc[i0 + m] = adc_code(w[m], gain, pedestal, sigma, (float)n[m], top);
+    } else {
+        // the filtered noise through LDS (in place of the deviates) to the threads
+        // that hold the samples
+        float *nf = (float *)fir_lds;
+        __syncthreads();
+        if (filters) {
+#pragma unroll
+            for (int m = 0; m < kFirPer; ++m)
+                nf[m * stride + tid] = (float)n[m];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < kFirPer; ++m) {
+            const int c = tid + m * (int)blockDim.x;
+            if ((!MORE || c < T) && t0 + c < ncols)
+                adc[row * ncols + t0 + c] =
+                    adc_code(w[m], gain, pedestal, sigma,
+                             nf[(c & (kFirPer - 1)) * stride + c / kFirPer], top);
+        }
     }
 }
 
@@ -2377,15 +2424,30 @@ hipError_t launch_digitize_fir(const float *wave, int64_t nrows, int64_t ncols, 
             best = cost;
         }
     }
+    // A launch that leaves most of the chip idle lasts as long as one workgroup: twice the
+    // threads then share its draws and samples (the filter keeps eight columns a
+    // thread), and short filters, whose workgroups are all draws, take 1024 columns
+    // unless that alone makes it more than one workgroup a CU.  400 rows of 1001
+    // columns, one tap: 7.5 -> 6.3 us, 64 taps 10.3 -> 9.0; 200 x 3001, one tap 8.1 -> 7.2 (256
+    // taps 18.1 -> 19.0, so not there); 200 x 2000, one tap 5.0 -> 5.6, so not there; 960 x
+    // 1001, 64 taps 10.3 -> 11.4.
+    const int64_t cus = device_cus(), few = nfir <= 32 ? 3 * cus : 2 * cus;
+    auto launch_blocks = [&](int t) { return nrows * ((ncols + t - 1) / t); };
+    if (nfir <= 32 && T > 1024 && launch_blocks(1024) <= few &&
+        (launch_blocks(1024) <= cus || launch_blocks(T) > cus))
+        T = 1024;
     const int64_t tiles = (ncols + T - 1) / T, blocks = nrows * tiles;
+    const bool more = T <= 1024 && blocks <= few;
     const int nz = T + hist;
     const size_t lds =
         sizeof(double) * kFirPer * (size_t)(nz / kFirPer / 8 * 8 + 8 + kFirPad);
     const bool vec = ncols % kFirPer == 0 && ((uintptr_t)wave & 15) == 0 &&
                      ((uintptr_t)adc & 15) == 0;
-    auto *kernel = vec ? k_digitize_fir<true> : k_digitize_fir<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(T / kFirPer), lds, s, wave, nrows,
-                       ncols, tiles, gain, pedestal, sigma, fir, nfir, (float)((1 << bits) - 1),
+    auto *kernel = vec ? (more ? k_digitize_fir<kRowsWhole, true> : k_digitize_fir<kRowsWhole, false>)
+                   : blocks > kFirShared * cus ? k_digitize_fir<kRowsSingle, false>
+                   : more ? k_digitize_fir<kRowsShared, true> : k_digitize_fir<kRowsShared, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(T / kFirPer * (more ? 2 : 1)), lds, s,
+                       wave, nrows, ncols, tiles, gain, pedestal, sigma, fir, nfir, (float)((1 << bits) - 1),
                        (uint32_t)seed ^ 0x6e6f6973u, (uint32_t)(seed >> 32), event, adc);
     return hipGetLastError();
 }
@@ -2568,23 +2630,6 @@ size_t raster_work_bytes(const wcsim_plane *pl, int64_t n)
 RasterWork raster_work_carve(const wcsim_plane *pl, int64_t n, void *base)
 {
     return raster_work_carve_batch(pl, n, pl->ntiles, occ_bands(pl->Np), base);
-}
-
-// Compute units of the current device (cached per device).
-int device_cus()
-{
-    static std::atomic<int> cus[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return 256;
-    int v = cus[dev].load(std::memory_order_relaxed);
-    if (v <= 0) {
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            v <= 0)
-            v = 256;
-        cus[dev].store(v, std::memory_order_relaxed);
-    }
-    return v;
 }
 
 // The colour lists (in depo_tile, free once the records are written: a tile

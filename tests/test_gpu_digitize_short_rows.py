@@ -56,3 +56,20 @@ def test_taps_past_the_row_cost_nothing():
         times.append(float(np.median(v)))
         print("%d taps: %.1f us" % (nfir, times[-1]), flush=True)
     assert times[1] < 1.5 * times[0]
+
+
+@pytest.mark.parametrize("rows,ncols,nfir", [(1, 1001, 1), (3, 3001, 32), (3, 3001, 33), (512, 1000, 33),
+                                             (513, 1000, 33), (768, 1001, 32), (769, 1001, 32),
+                                             (300, 2049, 5), (1, 513, 513), (1280, 1001, 9),
+                                             (1281, 1001, 9)])
+def test_codes_of_few_and_many_workgroups(rows, ncols, nfir):
+    """On both sides of the launch sizes where a workgroup gets more threads or
+    fewer columns; whole and ragged groups of eight columns."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(rows)
+    w = (rng.standard_normal((rows, ncols)) * 400.0).astype(np.float32)
+    f = (rng.standard_normal(nfir) / np.sqrt(nfir)).astype(np.float32)
+    ref = O.digitize(w, 1.25, 700.0, 3.0, 13, SEED, 4, fir=f.astype(np.float64))
+    got = _digitize(torch.from_numpy(w).cuda(), torch.from_numpy(f).cuda())
+    assert np.array_equal(got.cpu().numpy().view(np.uint16), ref)
