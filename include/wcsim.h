@@ -124,8 +124,9 @@ typedef struct {
                          * so N' <= 20000 (else WCSIM_E_INVALID) */
     int32_t fft_pitch;  /* pitch-axis overlap-save block transform length L > resp_npitch - 1 */
     int32_t freq_chunk; /* spectrum columns per chunk (8 or 16); 0: by the transform
-                         * lengths alone, so that planes of one readout and response
-                         * run in one batch launch whatever their wires */
+                         * lengths and `deterministic` alone, so that planes of one
+                         * readout and response run in one batch launch whatever
+                         * their wires */
     int32_t tile;       /* raster tile shape id, pitch bins x ticks of a tile: 0 = 32 x 8
                          * (default), 1 = 32 x 32, 2 = 64 x 8; each wavefront's LDS
                          * region adds a 32-bin x 16-tick halo */

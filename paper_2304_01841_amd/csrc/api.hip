@@ -197,19 +197,23 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
     // history is Rp - 1 of the L rows).
     int L = (sc && sc->fft_pitch) ? sc->fft_pitch
                                   : std::min(2048, std::max(256, pow2_at_least(4 * pl->Rp)));
-    // Default chunk with long pitch blocks: 16 columns for tick transforms of 4096
+    // Default chunk with long pitch blocks: 16 columns for tick transforms of 1200
     // points or more, else 8.  Sixteen make whole 128-byte lines of each pitch row
     // (with 8 the two halves of a line are written and read by workgroups of
-    // different L2s, which costs once the spectrum goes out to HBM); eight give the
-    // pitch passes twice the workgroups.  The rule looks at the length alone: planes
-    // that differ in their wires only have to share batch launches and response
-    // spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 233 / 197 us, 300 x
-    // 6000 72 / 67, 24 x 6000 33 / 32, 960 x 4500 179 / 153, 24 x 4500 33 / 31; below
-    // the line 960 x 3000 123 / 113, 480 x 3000 66 / 66, 100 x 3000 34 / 37, 24 x 3000
-    // 28 / 32, 100 x 1000 22 / 25.  Pitch output 960 x 6000 407 / 374, 480 x 3000 114 /
-    // 113.  A batch of 16 events on 100-960 wires x 6000 ticks: 8 columns 2380 us, 16
-    // 1910, 8 for its 100-wire planes and 16 for the others (two classes) 1990.
-    pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && pl->N2 < 2048 ? 8 : 16);
+    // different L2s, which costs once the spectrum goes out to HBM); the pass of the
+    // wire output takes them by halves where it needs more workgroups.  The rule does not
+    // look at the wires: planes that differ in those only have to share batch launches and
+    // response spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 233 / 192 us,
+    // 300 x 6000 72 / 67, 24 x 6000 33 / 31, 960 x 3000 123 / 117, 480 x 3000 66 / 66, 24 x 3000
+    // 28 / 27, 960 x 1500 63 / 59, 300 x 1000 28.4 / 29.7, 100 x 1000 22.1 / 22.2.  Pitch output
+    // 960 x 6000 407 / 374, 480 x 3000 114 / 113, 800 x 830 (fewer than 40 chunks for
+    // eight XCDs) 59 / 64.  A batch of 16 events on 100-960 wires, 8 / 16 columns / both in
+    // two classes: 6000 ticks 2380 / 1915 / 1995 us, 3000 ticks 1415 / 1310 / 1372, 1000
+    // ticks 817 / 731.  With reproducible sums the wire pass has no halves or groups: 16
+    // columns from 3600 points on (960 x 6000 232 / 192, 24 x 6000 41.5 / 44.5, 960 x 3851 160 /
+    // 136, 100 x 3851 45 / 51; 960 x 3000 122 / 116, 24 x 3000 38.5 / 41.8, 100 x 1000 34.7 / 37.1).
+    const int wide_from = (sc && sc->deterministic == 1) ? 1800 : 600;
+    pl->F = (sc && sc->freq_chunk) ? sc->freq_chunk : (L >= 1024 && pl->N2 < wide_from ? 8 : 16);
     pl->wide_by_choice =
         donor ? donor->wide_by_choice : !(sc && sc->freq_chunk) && L >= 1024 && pl->F == 16;
     if (pl->F != 8 && pl->F != 16)
@@ -908,9 +912,9 @@ wcsim_status wcsim_simulate_event_profiled(const wcsim_plane *pl, const wcsim_de
 // ---------------------------------------------------------------------------
 // The array is longer than the limit by what a plane of chosen 16-column chunks may
 // need beyond it (wcsim_plane::wide_by_choice): at most 8 columns of both spectra.
-// Such a plane has L >= 1024 and spectra of 2048 columns or more (the rule of
-// choose_schedule), of which 8 are below 1 / 256 of the limit, 256 KiB.
-constexpr size_t kScratchSlack = 512u << 10;
+// Such a plane has spectra of more than 600 columns (the rule of choose_schedule), of
+// which 8 are below 1 / 75 of the limit, 874 KiB.
+constexpr size_t kScratchSlack = 1u << 20;
 static __device__ __align__(256) unsigned char scratch[WCSIM_NOALLOC_SCRATCH_BYTES + kScratchSlack];
 
 namespace {

@@ -1153,7 +1153,9 @@ struct PolyIo {
     int Nw, nblocks;
 };
 
-template <int F, int S, bool BATCH>
+// F columns a workgroup, of chunks of FS: with FS = 2 F the two halves of a block
+// follow one another on one XCD.
+template <int F, int FS, int S, bool BATCH>
 __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables bt, int C, int D,
                                                           int A, int cw, const float2 *twM)
 {
@@ -1163,7 +1165,12 @@ __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables
     __shared__ float2 tab[NTAB];
     const int grp = (S > 1) ? (int)threadIdx.x / NT : 0;
     float2 *buf = bufs[grp];
-    int gblk = blockIdx.x;
+    static_assert(FS == F || FS == 2 * F, "a chunk or its half");
+    int gblk = blockIdx.x, col0 = 0;
+    if (FS > F) {  // (blocks come in eights, one per XCD)
+        col0 = ((gblk >> 3) & 1) * F;
+        gblk = (gblk >> 4) * 8 + (gblk & 7);
+    }
     if (BATCH) {
         const int e = find_event(bt.pblk_base, bt.nev, gblk);
         const EventCtx &E = bt.ev[e];
@@ -1185,8 +1192,8 @@ __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables
     const int V = M - A + 1, w0 = blk * V;
     const int tid = threadIdx.x - grp * NT;
     const int s = tid % F, i = tid / F;  // radix-16 butterfly i < 8 of column s
-    const gptr<const float2> Xc = glb(io.X) + (int64_t)c * io.Np * F;
-    const gptr<const float2> Hc = glb(io.H) + (int64_t)c * D * M * F;
+    const gptr<const float2> Xc = glb(io.X) + (int64_t)c * io.Np * FS + col0;
+    const gptr<const float2> Hc = glb(io.H) + (int64_t)c * D * M * FS + col0;
     float2 acc[16];
 #pragma unroll
     for (int t = 0; t < 16; ++t)
@@ -1200,16 +1207,16 @@ __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables
         auto load = [&](int col, int j) {
             const int q = (m0 + j) * D + phi;
             const int qc = min(max(q, 0), io.Np - 1);
-            const float2 v = Xc[(int64_t)qc * F + col];
+            const float2 v = Xc[(int64_t)qc * FS + col];
             return (q == qc) ? v : make_float2(0.0f, 0.0f);
         };
         ct_pass<M, 8, 1, NSS, 1, F, NT, true, false>(buf, tab, load, none, tid);
         // radix-16 pass (p = 8) into registers, then times H_b, summed over b
-        const gptr<const float2> Hb = Hc + (int64_t)b * M * F;
+        const gptr<const float2> Hb = Hc + (int64_t)b * M * FS;
         float2 h[16], v[16];
 #pragma unroll
         for (int t = 0; t < 16; ++t)
-            h[t] = Hb[(i + 8 * t) * F + s];
+            h[t] = Hb[(i + 8 * t) * FS + s];
 #pragma unroll
         for (int t = 0; t < 16; ++t)
             v[t] = buf[(i + 8 * t) * F + s];
@@ -1241,13 +1248,13 @@ __global__ __launch_bounds__(8 * F * S) void k_pitch_poly(PolyIo io, BatchTables
     for (int t = 0; t < 16; ++t)
         buf[(i + 8 * t) * F + s] = conjf2(acc[t]);
     __syncthreads();
-    const gptr<float2> Yc = glb(io.Y) + (int64_t)c * io.Nw * F;
+    const gptr<float2> Yc = glb(io.Y) + (int64_t)c * io.Nw * FS + col0;
     const int nw = io.Nw;
     auto store = [&](int col, int j, float2 val) {
         const int w = w0 + j - (A - 1);
         if (j < A - 1 || w >= nw || grp != 0)
             return;
-        Yc[(int64_t)w * F + col] = conjf2(val);
+        Yc[(int64_t)w * FS + col] = conjf2(val);
     };
     ct_fft<M, NSS, 1, F, NT, 1, InLds, decltype(store), 8, 16>(buf, tab, none, store, tid);
 }
@@ -1643,15 +1650,16 @@ int poly_blocks_total(const wcsim_plane *pl)
     return 8 * ((pl->C + 7) / 8) * pl->polyBlocks;
 }
 
-template <int F, int S, bool B>
+template <int F, int FS, int S, bool B>
 void launch_poly(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt, unsigned blocks,
                  hipStream_t s)
 {
-    hipLaunchKernelGGL((k_pitch_poly<F, S, B>), dim3(blocks), dim3(8 * F * S), 0, s, io, bt, pl->C,
-                       (int)pl->kp.nimpact, pl->polyA, pl->polyCw, pl->twP);
+    hipLaunchKernelGGL((k_pitch_poly<F, FS, S, B>), dim3(blocks * (FS / F)), dim3(8 * F * S), 0, s, io,
+                       bt, pl->C, (int)pl->kp.nimpact, pl->polyA, pl->polyCw, pl->twP);
 }
 
-// The polyphase pitch pass of one plane (io set) or of a batch (tables).  The
+// The polyphase pitch pass of one plane (io set) or of a batch (tables); `blocks`
+// counts whole chunks.  The
 // phases are cut over five groups while the launch has at most one workgroup per
 // CU (a CU then holds nothing else, and five groups of 16 columns fill 82 KB of its
 // LDS), over two while it has at most six per CU with 8 columns or four with 16
@@ -1663,20 +1671,28 @@ void launch_poly(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt,
 // 80.3 / 72.6 / 88.5, 1000 114 / 112 / 128, 1368 153 / 158 / 184.  A plane of
 // reproducible sums keeps one group, so that its sums do not depend on what shares
 // the launch; other planes' sums are rounded in the order of the groups.
+// Chunks of 16 columns go by halves where twice the workgroups still have a CU each
+// (five groups, eight / sixteen columns a workgroup: 100 wires x 1000 ticks 22.4 / 25.3
+// us, 24 x 3000 28.3 / 31.5, 300 x 1000 28.4 / 32.6; past that 200 x 2000 41.7 / 38.2).  With
+// one group the halves lose: a wavefront alone waits for each phase's rows, which it
+// no longer finds in the lines of the phase before (100 x 3851, reproducible sums: chunks
+// of 8 columns 44.7 us, halves of 16 50.6).
 template <bool B>
 hipError_t poly_any(const wcsim_plane *pl, const PolyIo &io, const BatchTables &bt,
                     unsigned blocks, hipStream_t s)
 {
     const unsigned cus = (unsigned)device_cus();
     const int S = (pl->det || blocks > (pl->F == 16 ? 4 : 6) * cus) ? 1 : (blocks > cus) ? 2 : 5;
-    if (pl->F == 16)
-        S == 1   ? launch_poly<16, 1, B>(pl, io, bt, blocks, s)
-        : S == 2 ? launch_poly<16, 2, B>(pl, io, bt, blocks, s)
-                 : launch_poly<16, 5, B>(pl, io, bt, blocks, s);
+    if (pl->F == 8)
+        S == 1   ? launch_poly<8, 8, 1, B>(pl, io, bt, blocks, s)
+        : S == 2 ? launch_poly<8, 8, 2, B>(pl, io, bt, blocks, s)
+                 : launch_poly<8, 8, 5, B>(pl, io, bt, blocks, s);
+    else if (S == 5 && 2 * blocks <= cus)
+        launch_poly<8, 16, 5, B>(pl, io, bt, blocks, s);
     else
-        S == 1   ? launch_poly<8, 1, B>(pl, io, bt, blocks, s)
-        : S == 2 ? launch_poly<8, 2, B>(pl, io, bt, blocks, s)
-                 : launch_poly<8, 5, B>(pl, io, bt, blocks, s);
+        S == 1   ? launch_poly<16, 16, 1, B>(pl, io, bt, blocks, s)
+        : S == 2 ? launch_poly<16, 16, 2, B>(pl, io, bt, blocks, s)
+                 : launch_poly<16, 16, 5, B>(pl, io, bt, blocks, s);
     return hipGetLastError();
 }
 

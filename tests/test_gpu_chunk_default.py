@@ -21,16 +21,19 @@ def _chunks(wcsim, planes):
     return wcsim._lib.wcsim_batch_chunk_count(p, n, len(planes), wcsim.OUT_WIRE)
 
 
-# (3851 ticks: 4050-point transforms, the longest below 4096; 3852: 4096)
-@pytest.mark.parametrize("ticks", [300, 1000, 2000, 3000, 3851, 3852, 6000])
-def test_one_class_of_any_wire_count(ticks):
+# (953 and 3257 ticks: 1152- and 3456-point transforms, the longest below 1200 and
+# 3600)
+@pytest.mark.parametrize("det", [0, 1])
+@pytest.mark.parametrize("ticks", [300, 953, 954, 2000, 3000, 3257, 3258, 6000])
+def test_one_class_of_any_wire_count(ticks, det):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2304_01841_amd import wcsim
     phys, R = W.physics(True), W.response("bipolar")
-    planes = [wcsim.Plane(W.plane(w, ticks), phys, R) for w in WIRES]
+    sched = {"deterministic": det}
+    planes = [wcsim.Plane(W.plane(w, ticks), phys, R, schedule=sched) for w in WIRES]
     widths = {p.info["freq_chunk"] for p in planes}
-    assert widths == {16 if ticks >= 3852 else 8}
+    assert widths == {16 if ticks >= (3258 if det else 954) else 8}
     assert _chunks(wcsim, planes) == 1
     for donor in (planes[0], planes[-1]):
         for w in WIRES:

@@ -27,7 +27,7 @@ def _most(wcsim, P, kind):
     return lo
 
 
-@pytest.mark.parametrize("wires,ticks", [(100, 6000), (130, 4000), (60, 9000)])
+@pytest.mark.parametrize("wires,ticks", [(100, 6000), (130, 4000), (60, 9000), (480, 1050)])
 def test_limit_is_that_of_eight_columns(wires, ticks):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -58,3 +58,30 @@ def test_two_groups_of_sixteen_columns(wires, ticks, nimpact):
     got = wcsim.convolve(P, torch.from_numpy(G).cuda()).cpu().numpy()
     assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
     P.destroy()
+
+
+@pytest.mark.parametrize("nimpact", [2, 5, 10, 11])
+@pytest.mark.parametrize("wires,ticks", [(3, 2000), (110, 1000), (240, 900), (330, 1000)])
+def test_halves_of_sixteen_columns(wires, ticks, nimpact):
+    """Chunks of sixteen columns, one to three blocks of wires, on both sides of
+    the launches that take them by halves, alone and in a batch."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2304_01841_amd import wcsim
+    rng = np.random.default_rng(wires + nimpact)
+    Rp = min(21 * nimpact, 60)
+    R = W.random_response(rng, Rp, 30)
+    P = wcsim.Plane(W.plane(wires, ticks, nimpact=nimpact), W.physics(False), R, r0=Rp // 3,
+                    schedule={"freq_chunk": 16, "wire_mode": 1})
+    G = rng.standard_normal((wires * nimpact, ticks)).astype(np.float32)
+    ref = O.wire_rows(O.convolve(G, R.astype(np.float64), Rp // 3, workers=8), nimpact)
+    got = wcsim.convolve(P, torch.from_numpy(G).cuda()).cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+    dep = torch.from_numpy(W.uniform_depos(rng, 500, (0.0, wires * W.PITCH), (0.0, ticks * W.TICK))).cuda()
+    alone = wcsim.simulate_event(P, dep, 5)
+    for n in (1, 2, 6):
+        outs = [torch.full((wires, ticks), float("nan"), device="cuda") for _ in range(n)]
+        wcsim.simulate_batch([P] * n, [dep] * n, [5] * n, outs)
+        for o in outs:
+            assert (o - alone).abs().max() <= 1e-5 * alone.abs().max()
+    P.destroy()
