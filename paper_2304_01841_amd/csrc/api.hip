@@ -204,8 +204,9 @@ wcsim_status choose_schedule(wcsim_plane *pl, const wcsim_schedule *sc, const wc
     // wire output takes them by halves where it needs more workgroups.  The rule does not
     // look at the wires: planes that differ in those only have to share batch launches and
     // response spectra.  Wire output, 8 / 16 columns: 960 wires x 6000 ticks 233 / 192 us,
-    // 300 x 6000 72 / 67, 24 x 6000 33 / 31, 960 x 3000 123 / 117, 480 x 3000 66 / 66, 24 x 3000
-    // 28 / 27, 960 x 1500 63 / 59, 300 x 1000 28.4 / 29.7, 100 x 1000 22.1 / 22.2.  Pitch output
+    // 300 x 6000 72 / 67, 24 x 6000 32 / 31, 960 x 3000 123 / 117, 480 x 3000 66 / 66, 24 x 3000
+    // 28 / 28, 960 x 1500 63 / 61, 480 x 1000 36.0 / 34.0, 300 x 1000 28.4 / 30.0, 100 x 1000
+    // 23.0 / 22.9.  Pitch output
     // 960 x 6000 407 / 374, 480 x 3000 114 / 113, 800 x 830 (fewer than 40 chunks for
     // eight XCDs) 59 / 64.  A batch of 16 events on 100-960 wires, 8 / 16 columns / both in
     // two classes: 6000 ticks 2380 / 1915 / 1995 us, 3000 ticks 1415 / 1310 / 1372, 1000
